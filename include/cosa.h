@@ -218,8 +218,8 @@ cosa_status cosa_osk_attention(const cosa_problem* problem, const void* q, const
                                float* margin_log, int32_t* n_computed, void* stream);
 
 /*
- * cosa_osk_attention as cosa_prefill runs it: a persistent grid of one workgroup per compute unit
- * that takes (query block, head pair) tiles from eight work queues, one per XCD, heaviest query
+ * cosa_osk_attention as cosa_prefill runs it: a persistent grid that fills the compute units and
+ * takes (query block, head pair) tiles from eight work queues, one per XCD, heaviest query
  * blocks first; a workgroup drains its own XCD's queue, then the others. Same arguments, results
  * and logs as cosa_osk_attention, bit for bit. queue: device memory of at least
  * cosa_osk_attention_queue_bytes() bytes, 4-byte aligned, owned by the caller; its contents are

@@ -1,0 +1,84 @@
+"""How the attention kernels place tiles on workgroups: head counts, block counts and block sizes at
+the edges of the dispatch, against the float64 oracle.
+
+The list walk (one workgroup per tile, and the persistent grid on a work queue), the masked walk and
+the dense walk run on the same small problems. Skip decisions and computed counts must equal the
+oracle's except within 1e-4 of the threshold, outputs lie within the path's bound (tests/parity.py),
+and the two launches of the list walk agree bit for bit.
+"""
+import math
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import cosa_oracle as O
+from paper_2607_25291_amd import binding as B
+from paper_2607_25291_amd.inputs import random_inputs
+from tests import parity as PR
+from tests.gpu_util import Run, bf16_to_f64, dev, host_bits, tau_of, torch
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+# batch, query heads, KV heads, block, blocks
+CASES = [
+    # an odd group size: one head per workgroup, one page buffer (both block sizes, one block up)
+    (1, 1, 1, 128, 1), (1, 3, 1, 128, 2), (2, 3, 3, 128, 5), (1, 5, 1, 64, 3), (1, 7, 1, 64, 9),
+    # two heads per workgroup, 64-token blocks: two workgroups per compute unit
+    (1, 2, 1, 64, 1), (2, 8, 2, 64, 7),
+]
+
+
+def random_lists(rng, Bt, H, nb):
+    """A random subset of the candidates of every row in random order, the block itself among them."""
+    order = np.full((Bt, H, nb, nb), -1, np.int32)
+    count = np.zeros((Bt, H, nb), np.int32)
+    for n, g, i in np.ndindex(Bt, H, nb):
+        k = int(rng.integers(1, i + 2))
+        pick = np.concatenate([[i], rng.permutation(i)[:k - 1]]).astype(np.int32)
+        order[n, g, i, :k] = rng.permutation(pick)
+        count[n, g, i] = k
+    return order, count
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "b%d_q%d_kv%d_blk%d_nb%d" % c)
+def test_walks_match_oracle(case):
+    Bt, Hq, Hkv, block, nb = case
+    say(f"[tiles] B={Bt} Hq={Hq} Hkv={Hkv} block={block} nb={nb}")
+    L = nb * block
+    q, k, v = random_inputs(Bt, Hq, Hkv, L, 128, seed=nb, scale=1.5)
+    p = B.Problem(Bt, Hq, Hkv, L, 128, block, block // 8)
+    run = Run.upload(p, q, k, v)
+    order, count = random_lists(np.random.default_rng(Hq * 100 + nb), Bt, Hkv, nb)
+    delta = L * math.exp(-1.0)
+    ref = O.osk_attention(q, k, v, order, count, block=block, skip_mode=O.SKIP_ROWMAX, delta=delta)
+    do, dc = dev(order), dev(count)
+    sk = B.skip(B.SKIP_ROWMAX, delta)
+    o, vis, _, nco = run.osk(do, dc, sk)
+    vis = vis.cpu().numpy()
+    for n, h, i in np.ndindex(Bt, Hq, nb):
+        PR.check_visits(vis[n, h, i], ref["visit"][n, h, i], ref["margin"][n, h, i],
+                        tau_of(delta, L), int(count[n, h * Hkv // Hq, i]))
+    PR.check_output(bf16_to_f64(host_bits(o)), ref["o"])
+
+    t = torch()
+    queue = t.full((B.cosa_osk_attention_queue_bytes(),), 0xFF, dtype=t.uint8, device="cuda")
+    oq, nq = t.full_like(o, 0x7BCD), t.full_like(nco, -1)
+    B.cosa_osk_attention_queued(p, run.q, run.k, run.v, do, dc, sk, oq, queue, queue.numel(),
+                                n_computed=nq)
+    assert t.equal(o, oq) and t.equal(nco, nq)
+
+    mask = np.zeros((Bt, Hkv, nb, nb), np.uint8)
+    for n, g, i in np.ndindex(Bt, Hkv, nb):
+        mask[n, g, i, order[n, g, i, :count[n, g, i]]] = 1
+    ref_m = O.osk_attention(q, k, v, order, count, block=block, skip_mode=O.SKIP_NONE)["o"]
+    om = t.full_like(o, 0x7BCD)
+    B.cosa_masked_attention(p, run.q, run.k, run.v, dev(mask), om)
+    PR.check_output(bf16_to_f64(host_bits(om)), ref_m)
+    PR.check_output(bf16_to_f64(host_bits(run.dense())), O.dense_attention(q, k, v, block=block))
