@@ -46,6 +46,7 @@
 //               for k = 0..3, element i % 4 of the 8 bytes addressed by lane 4k + i / 4. Lane i
 //               addressing V[key0 + i/4][d0 + 4 (i%4)] therefore receives keys key0..key0+3 of
 //               column d0 + i, which is the P^T key set that lane holds from the S^T accumulators.
+#include <algorithm>
 #include <type_traits>
 
 #include "cosa_device.h"
@@ -73,8 +74,42 @@ constexpr int kLgkm0 = 0xC07F;
 struct AttnParams {
   AttnArgs a;
   int Hq, Hkv, L, nb, G, n_units;
+  int group_heads;       // (batch, KV head) pairs whose query blocks are walked together (unit_tile)
   float scale, scale_log2;
+  PackOrder pack_order;  // packed sequences only
 };
+
+// The query block i of (batch, KV head) ng that unit u stands for, with the first block F and the
+// index of the packed sequence that holds it. The heads go in groups of P.group_heads; in a group the
+// heaviest query blocks of every head come first, so that its last tiles are the lightest ones and
+// the CUs finish together. With whole heads one after the other, the last head's heaviest blocks
+// started when the others were done (dense, 32 / 8 heads, 4K tokens 190 -> 131 us, 8K 577 -> 478 us).
+// A block's weight is its position in its sequence; packed sequences are ranked over all of them.
+__device__ __forceinline__ void unit_tile(const AttnParams& P, int u, int& ng, int& i, int& F,
+                                          int& seq) {
+  const int gsz = P.group_heads * P.nb;
+  const int grp = u / gsz, r = u - grp * gsz;
+  const int first = grp * P.group_heads;
+  const int heads = min(P.group_heads, P.n_units / P.nb - first);
+  const int rank = r / heads;
+  ng = first + (r - rank * heads);
+  F = 0;
+  seq = 0;
+  i = P.nb - 1 - rank;
+  if (P.a.pack.n > 0) {
+    int lo = 0, hi = P.a.pack.n - 1;  // the last piece that starts at or before the rank
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (P.pack_order.start[mid] <= rank) lo = mid;
+      else hi = mid - 1;
+    }
+    const int off = rank - P.pack_order.start[lo], down = off / (lo + 1);
+    const int shortest = P.pack_order.by_len[lo];  // of the lo + 1 sequences that reach the piece
+    seq = P.pack_order.by_len[off - down * (lo + 1)];
+    F = P.a.pack.cu[seq];
+    i = F + (P.a.pack.cu[shortest + 1] - P.a.pack.cu[shortest]) - down - 1;
+  }
+}
 
 template <int BLOCK, int HPW>
 struct TileCfg {
@@ -273,8 +308,10 @@ void attention_kernel(const AttnParams P) {
   } else {
     if (!map_tile(blockIdx.x, P.G / HPW, P.n_units, unit, pair)) return;
   }
-  const int i = P.nb - 1 - (unit % P.nb);  // heaviest query blocks first
-  const int ng = unit / P.nb;              // n * Hkv + g
+  // Packed sequences: block i only sees the blocks F .. i of its own sequence, whose skip threshold
+  // is its own (F = 0 and the call's threshold without packing; the masked walk is never packed).
+  int ng, i, F, seq;  // ng = n * Hkv + g
+  unit_tile(P, unit, ng, i, F, seq);
   const int g = ng % P.Hkv, n = ng / P.Hkv;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, scalar
@@ -299,11 +336,6 @@ void attention_kernel(const AttnParams P) {
     for (int c = 0; c < 8; ++c) qf[c] = as_bf16x8(ldg16(qp + 16 * c));
   }
 
-  // Packed sequences: block i only sees the blocks F .. i of its own sequence, whose skip
-  // threshold is its own (F = 0 and the call's threshold without packing; the masked walk is
-  // never packed).
-  int seq;
-  const int F = pack_first(P.a.pack, i, seq);
   const float tau = P.a.pack.n > 0 ? P.a.pack.tau[seq] : P.a.tau;
   int cnt;
   const int32_t* lst = nullptr;
@@ -705,23 +737,54 @@ void attention_kernel(const AttnParams P) {
   }  // tiles of a persistent workgroup
 }
 
+int cu_count() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+    return 256;
+  return cus;
+}
+
+// Heads whose query blocks are walked together (unit_tile). Eight, one per XCD, so that each XCD's L2
+// serves one head's pages at a time: with more, or with whole heads one after the other over all
+// XCDs, long contexts lose that (16 / 16 heads, 64K tokens: 3.49 ms one at a time, 2.95 by eights, 3.21
+// all at once). More, in whole eights, while a group has fewer than four tiles per resident
+// workgroup, where the idle end of every group costs more (16 / 16 heads, 12,416 tokens: 166 us by
+// eights, 162 all at once; 4K tokens 52 and 48).
+int heads_per_group(const Shape& sh, int tiles_per_unit, int resident) {
+  const int heads = sh.B * sh.Hkv;
+  long long g = 8;
+  while (g < heads && g * sh.nb * tiles_per_unit < 4LL * resident) g += 8;
+  return (int)(g < heads ? g : heads);
+}
+
+PackOrder order_of(const SeqPack& sp) {
+  PackOrder po;
+  auto len = [&](int q) { return sp.cu[q + 1] - sp.cu[q]; };
+  for (int q = 0; q < sp.n; ++q) po.by_len[q] = q;
+  std::stable_sort(po.by_len, po.by_len + sp.n, [&](int x, int y) { return len(x) > len(y); });
+  for (int k = 0, at = 0; k < sp.n; ++k) {
+    po.start[k] = at;
+    const int next = k + 1 < sp.n ? len(po.by_len[k + 1]) : 0;
+    at += (k + 1) * (len(po.by_len[k]) - next);
+  }
+  return po;
+}
+
 template <int BLOCK, int HPW, int WALK, int PG>
-void launch_t(const AttnParams& P, int G, hipStream_t stream) {
+void launch_t(const Shape& sh, AttnParams& P, int cus, hipStream_t stream) {
   using Cfg = TileCfg<BLOCK, HPW>;
-  const int slots = (P.n_units + kNumXcd - 1) / kNumXcd * kNumXcd * (G / HPW);
+  const int slots = (P.n_units + kNumXcd - 1) / kNumXcd * kNumXcd * (sh.G / HPW);
+  const int resident = cus * Cfg::kWgPerCu;
+  P.group_heads = heads_per_group(sh, sh.G / HPW, resident);
   if constexpr (WALK == kWalkList) {
     if (P.a.queue != nullptr) {
       // As many workgroups as the LDS footprint admits, fed by the work queues: one per CU for head
       // pairs of b = 128, two for pairs of b = 64 (packed 25K tokens, 16 / 4 heads: 288 -> 230 us
       // against one).
-      int dev = 0, cus = 0;
-      if (hipGetDevice(&dev) != hipSuccess ||
-          hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-          cus < 1)
-        cus = 256;
       hipLaunchKernelGGL(queue_reset, dim3(1), dim3(64), 0, stream, P.a.queue);
       hipLaunchKernelGGL((attention_kernel<BLOCK, HPW, WALK, PG, true>),
-                         dim3(cus * Cfg::kWgPerCu < slots ? cus * Cfg::kWgPerCu : slots), dim3(Cfg::kThreads), 0, stream, P);
+                         dim3(resident < slots ? resident : slots), dim3(Cfg::kThreads), 0, stream, P);
       return;
     }
   }
@@ -729,15 +792,22 @@ void launch_t(const AttnParams& P, int G, hipStream_t stream) {
                      dim3(Cfg::kThreads), 0, stream, P);
 }
 
+// Two heads per workgroup where the group size is even, unless there are so few tiles that a pair of
+// heads per CU or less is all there is: single heads then spread over the CUs, and a head's walk does
+// not wait for its partner's (dense, 4 / 1 heads, 8K tokens: 168 -> 135 us; prefill 32 / 8 heads, 2K
+// tokens 43 -> 40 us). Dense tiles of 64-token blocks keep the pairs (72 against 75 us at 4 / 1
+// heads, 4K tokens: their pages are short and the shared fetch counts more).
 template <int WALK, int PG>
-void launch_shape(const Shape& sh, const AttnParams& P, hipStream_t stream) {
-  const bool pair = (sh.G % 2) == 0;
+void launch_shape(const Shape& sh, AttnParams& P, hipStream_t stream) {
+  const int cus = cu_count();
+  const bool few = (long long)P.n_units * (sh.G / 2) <= cus && (sh.b == 128 || WALK == kWalkList);
+  const bool pair = (sh.G % 2) == 0 && !few;
   if (sh.b == 128) {
-    if (pair) launch_t<128, 2, WALK, PG>(P, sh.G, stream);
-    else launch_t<128, 1, WALK, PG>(P, sh.G, stream);
+    if (pair) launch_t<128, 2, WALK, PG>(sh, P, cus, stream);
+    else launch_t<128, 1, WALK, PG>(sh, P, cus, stream);
   } else {
-    if (pair) launch_t<64, 2, WALK, PG>(P, sh.G, stream);
-    else launch_t<64, 1, WALK, PG>(P, sh.G, stream);
+    if (pair) launch_t<64, 2, WALK, PG>(sh, P, cus, stream);
+    else launch_t<64, 1, WALK, PG>(sh, P, cus, stream);
   }
 }
 
@@ -745,6 +815,7 @@ template <int WALK>
 hipError_t launch(const Shape& sh, const AttnArgs& a, hipStream_t stream) {
   AttnParams P;
   P.a = a;
+  if (a.pack.n > 0) P.pack_order = order_of(a.pack);
   P.Hq = sh.Hq;
   P.Hkv = sh.Hkv;
   P.L = sh.L;

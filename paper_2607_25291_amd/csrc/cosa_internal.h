@@ -39,6 +39,14 @@ struct SeqPack {
   float tau[kMaxPackedSeqs];
 };
 
+// The blocks of all packed sequences by falling position in their sequence: by_len lists the sequences
+// by falling length, and the ranks start[k] .. start[k + 1] - 1 run over the positions that exactly
+// the k + 1 longest sequences have, position by position. Only read when pack.n > 0.
+struct PackOrder {
+  int by_len[kMaxPackedSeqs];
+  int start[kMaxPackedSeqs];
+};
+
 struct KapScoreArgs {
   const uint16_t* q;
   const uint16_t* k;   // contiguous K, or the paged K cache

@@ -32,6 +32,10 @@ CASES = [
     (1, 1, 1, 128, 1), (1, 3, 1, 128, 2), (2, 3, 3, 128, 5), (1, 5, 1, 64, 3), (1, 7, 1, 64, 9),
     # two heads per workgroup, 64-token blocks: two workgroups per compute unit
     (1, 2, 1, 64, 1), (2, 8, 2, 64, 7),
+    # groups of eight heads with a remainder, and heads that do not divide the XCDs
+    (1, 9, 9, 64, 6), (3, 6, 3, 128, 4), (1, 17, 17, 128, 3),
+    # the last block count at which even groups run as single heads (256 pairs), and the next one
+    (1, 32, 8, 128, 16), (1, 32, 8, 128, 17),
 ]
 
 
@@ -82,3 +86,35 @@ def test_walks_match_oracle(case):
     B.cosa_masked_attention(p, run.q, run.k, run.v, dev(mask), om)
     PR.check_output(bf16_to_f64(host_bits(om)), ref_m)
     PR.check_output(bf16_to_f64(host_bits(run.dense())), O.dense_attention(q, k, v, block=block))
+
+
+@pytest.mark.parametrize("lens", [(1,), (1, 1, 1), (5, 1, 5, 2, 3, 5), (2, 7, 4, 4, 1, 9, 6)],
+                         ids=lambda x: "-".join(map(str, x)))
+@pytest.mark.parametrize("heads,block", [((4, 2), 128), ((3, 3), 64), ((20, 10), 64)])
+def test_packed_tiles(lens, heads, block):
+    """Packed sequences, equal lengths and one-block ones among them: every block of every sequence
+    is visited (dense equals a call per sequence, and a prefill that keeps every block equals dense
+    attention)."""
+    Hq, Hkv = heads
+    say(f"[packed tiles] lens={lens} heads={heads} block={block}")
+    nb = sum(lens)
+    L = nb * block
+    q, k, v = random_inputs(1, Hq, Hkv, L, 128, seed=nb, scale=1.5)
+    cu = np.concatenate([[0], np.cumsum(lens)]).tolist()
+    p = B.Problem(1, Hq, Hkv, L, 128, block, block // 8)
+    run = Run.upload(p, q, k, v)
+    t = torch()
+    o = t.full_like(run.q, 0x7BCD)
+    B.cosa_dense_attention_varlen(p, B.varlen(cu), run.q, run.k, run.v, o)
+    for first, n in zip(cu, lens):
+        at = slice(first * block, (first + n) * block)
+        one = Run(B.Problem(1, Hq, Hkv, n * block, 128, block, block // 8),
+                  *(x[:, :, at].contiguous() for x in (run.q, run.k, run.v)))
+        assert t.equal(o[:, :, at], one.dense())
+    nbytes = B.cosa_prefill_workspace_bytes(p)
+    ws = t.zeros(nbytes, dtype=t.uint8, device="cuda")
+    op = t.full_like(run.q, 0x7BCD)
+    B.cosa_prefill_varlen(p, B.varlen(cu), run.q, run.k, run.v, B.select(B.SELECT_ALL), None, ws,
+                          nbytes, op)
+    ref = O.dense_attention_varlen(q, k, v, cu, block=block)
+    PR.check_output(bf16_to_f64(host_bits(op)), ref)
