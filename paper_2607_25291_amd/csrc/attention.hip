@@ -64,12 +64,6 @@ typedef short s16x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ int32_t ld_uniform(const int32_t* p) {
   return *(const __attribute__((address_space(4))) int32_t*)(size_t)p;
 }
-#define COSA_LDS(p) ((__attribute__((address_space(3))) void*)(p))
-
-// s_waitcnt immediates (vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8): wait for vector
-// memory and LDS operations, or for LDS operations only.
-constexpr int kVmcntLgkm0 = 0x0070;
-constexpr int kLgkm0 = 0xC07F;
 
 struct AttnParams {
   AttnArgs a;
@@ -124,32 +118,6 @@ struct TileCfg {
   static constexpr int kWgPerCu = (160 * 1024) / (kLdsBytes + 256);
   static constexpr int kWavesPerEu = (kWgPerCu * kWaves) / 4 > 1 ? (kWgPerCu * kWaves) / 4 : 1;
 };
-
-// Direct global -> LDS copy of one page by NW waves: wave w moves chunks c = u * NW + w (rows
-// 4c .. 4c+3). Lane l fills LDS slot l of the chunk (row 4c + l/16, stored slot l%16) with the
-// global slot that the layout puts there. The page offset and the chunk offset are scalars.
-template <int BLOCK, int NW, bool IS_K>
-__device__ __forceinline__ void copy_page(__amdgpu_buffer_rsrc_t rs, char* dst, int page_off,
-                                          int w, int lane) {
-  constexpr int kChunks = BLOCK * kHeadDim * 2 / 1024;
-  static_assert(kChunks % NW == 0, "page chunks must split evenly over the waves");
-  // The wave's first chunk in LDS and in the page. Kept opaque so that the per-chunk addresses are
-  // formed here (one scalar add each) instead of being held in registers across the page loop.
-  int lds0 = (int)(size_t)COSA_LDS(dst) + w * 1024;
-  int src0 = page_off + w * 1024;
-  asm volatile("" : "+s"(lds0), "+s"(src0));
-#pragma unroll
-  for (int u = 0; u < kChunks / NW; ++u) {
-    const int c = u * NW + w;
-    const int row = 4 * c + (lane >> 4);
-    const int stored = lane & 15;
-    const int slot = IS_K ? (stored ^ (row & 15)) : (stored ^ ((row & 3) << 2));
-    const int voff = (lane >> 4) * (kHeadDim * 2) + slot * 16;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(
-        rs, (__attribute__((address_space(3))) void*)(size_t)(lds0 + u * NW * 1024), 16, voff,
-        src0 + u * NW * 1024, 0, 0);
-  }
-}
 
 // Paged variant (Sec. 4.3 "Physical jumping over pages"): the block's rows live in physical pages of
 // 2^log2p >= 16 tokens of a [n_pages, Hkv, page, d] cache. Wave w moves the consecutive chunks
@@ -751,8 +719,8 @@ int cu_count() {
 // all at once). More, in whole eights, while a group has fewer than four tiles per resident
 // workgroup, where the idle end of every group costs more (16 / 16 heads, 12,416 tokens: 166 us by
 // eights, 162 all at once; 4K tokens 52 and 48).
-int heads_per_group(const Shape& sh, int tiles_per_unit, int resident) {
-  const int heads = sh.B * sh.Hkv;
+int heads_per_group(const Shape& sh, int heads_per_wg, int resident) {
+  const int heads = sh.B * sh.Hkv, tiles_per_unit = sh.G / heads_per_wg;
   long long g = 8;
   while (g < heads && g * sh.nb * tiles_per_unit < 4LL * resident) g += 8;
   return (int)(g < heads ? g : heads);
@@ -776,7 +744,7 @@ void launch_t(const Shape& sh, AttnParams& P, int cus, hipStream_t stream) {
   using Cfg = TileCfg<BLOCK, HPW>;
   const int slots = (P.n_units + kNumXcd - 1) / kNumXcd * kNumXcd * (sh.G / HPW);
   const int resident = cus * Cfg::kWgPerCu;
-  P.group_heads = heads_per_group(sh, sh.G / HPW, resident);
+  P.group_heads = heads_per_group(sh, HPW, resident);
   if constexpr (WALK == kWalkList) {
     if (P.a.queue != nullptr) {
       // As many workgroups as the LDS footprint admits, fed by the work queues: one per CU for head

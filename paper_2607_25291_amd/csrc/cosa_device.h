@@ -31,6 +31,43 @@ __device__ __forceinline__ bf16x8_t as_bf16x8(const u32x4_t& v) {
   return __builtin_bit_cast(bf16x8_t, v);
 }
 
+#define COSA_LDS(p) ((__attribute__((address_space(3))) void*)(p))
+
+// s_waitcnt immediates (vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8): wait for vector
+// memory and LDS operations, or for LDS operations only.
+constexpr int kVmcntLgkm0 = 0x0070;
+constexpr int kLgkm0 = 0xC07F;
+
+// Direct global -> LDS copy of one page by NW waves: wave w moves chunks c = u * NW + w (rows
+// 4c .. 4c+3). Lane l fills LDS slot l of the chunk (row 4c + l/16, stored slot l%16) with the
+// global slot that the layout puts there. The page offset and the chunk offset are scalars.
+template <int BLOCK, int NW, bool IS_K>
+__device__ __forceinline__ void copy_page(__amdgpu_buffer_rsrc_t rs, char* dst, int page_off,
+                                          int w, int lane) {
+  constexpr int kChunks = BLOCK * kHeadDim * 2 / 1024;
+  static_assert(kChunks % NW == 0, "page chunks must split evenly over the waves");
+  // The wave's first chunk in LDS and in the page. Kept opaque so that the per-chunk addresses are
+  // formed here (one scalar add each) instead of being held in registers across the page loop.
+  int lds0 = (int)(size_t)COSA_LDS(dst) + w * 1024;
+  int src0 = page_off + w * 1024;
+  asm volatile("" : "+s"(lds0), "+s"(src0));
+#pragma unroll
+  for (int u = 0; u < kChunks / NW; ++u) {
+    const int c = u * NW + w;
+    const int row = 4 * c + (lane >> 4);
+    const int stored = lane & 15;
+    const int slot = IS_K ? (stored ^ (row & 15)) : (stored ^ ((row & 3) << 2));
+    const int voff = (lane >> 4) * (kHeadDim * 2) + slot * 16;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+        rs, (__attribute__((address_space(3))) void*)(size_t)(lds0 + u * NW * 1024), 16, voff,
+        src0 + u * NW * 1024, 0, 0);
+  }
+}
+
+// IEEE maximum: no quieting of its inputs (fmaxf would first take each MFMA result's maximum with
+// itself); the two differ only on NaN inputs and on the sign of a zero result.
+__device__ __forceinline__ float vmax(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+
 // Cross-lane reductions without the LDS crossbar (ds_bpermute costs an LDS round trip per step):
 // v_permlane32_swap exchanges the two 32-lane halves, DPP moves data within rows of 16 lanes, and
 // v_readlane takes the last step into a scalar.

@@ -119,10 +119,6 @@ int proxy_slots(int NG, int nb) {
   return NG * nb;
 }
 
-// IEEE maximum: no quieting of its inputs (fmaxf would first take each MFMA result's maximum with
-// itself); the two differ only on NaN inputs and on the sign of a zero result.
-__device__ __forceinline__ float vmax(float a, float b) { return __builtin_elementwise_maximum(a, b); }
-
 // Sampled-key fragments of one 32-key chunk (MFMA A operand) for lane (half, l32): from the staged
 // copy through a buffer resource over the head's chunks (the chunk offset a scalar, the lane
 // offsets loop-invariant, so no address register is rewritten while loads into the fragment

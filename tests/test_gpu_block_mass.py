@@ -62,3 +62,18 @@ def test_block_mass_sampled_32k():
         np.testing.assert_allclose(got[n, g, i, :i + 1], ref[(n, g, i)], rtol=2e-4,
                                    atol=1e-5 * G * b)
         assert abs(got[n, g, i, :i + 1].sum() - G * b) < 1e-4 * G * b
+
+
+@pytest.mark.parametrize("heads,block,nb,batch", [
+    ((1, 1), 64, 1, 1), ((1, 1), 128, 1, 2), ((3, 1), 64, 5, 1), ((6, 2), 64, 3, 2),
+    ((10, 2), 128, 3, 1), ((2, 1), 128, 7, 1), ((8, 1), 64, 6, 1), ((12, 3), 128, 4, 1)])
+def test_block_mass_head_groups(heads, block, nb, batch):
+    """One, two and four query heads per workgroup, one and several passes over the group, both block
+    sizes and the first rows of the first block (whose lanes see masked keys only)."""
+    Hq, Hkv = heads
+    say(f"[block mass] heads={heads} block={block} nb={nb} batch={batch}")
+    w = Workload("m", batch, Hq, Hkv, nb * block, 128, block, block // 8, 0.5, 0.25, 64, 0.02)
+    q, k, _ = make_inputs(w)
+    got = gpu_mass(w, q, k)
+    ref = O.block_mass(q, k, n_kv_heads=Hkv, block=block)
+    np.testing.assert_allclose(got, ref, rtol=2e-4, atol=1e-5 * Hq // Hkv * block)
