@@ -719,9 +719,13 @@ int cu_count() {
 // all at once). More, in whole eights, while a group has fewer than four tiles per resident
 // workgroup, where the idle end of every group costs more (16 / 16 heads, 12,416 tokens: 166 us by
 // eights, 162 all at once; 4K tokens 52 and 48).
+// Four where head pairs walk contexts of which eight heads' K and V exceed the 256 MiB last-level
+// cache (32 / 8 heads, 128K tokens: 9.99 ms by eights, 9.95 by fours; single heads, whose pages
+// are read once per head, gain from eights there: 8 / 8 heads 3.37 and 3.44 ms).
 int heads_per_group(const Shape& sh, int heads_per_wg, int resident) {
   const int heads = sh.B * sh.Hkv, tiles_per_unit = sh.G / heads_per_wg;
-  long long g = 8;
+  const bool over_cache = 8LL * sh.L * kHeadDim * 4 > (256LL << 20);
+  long long g = heads_per_wg == 2 && over_cache ? 4 : 8;
   while (g < heads && g * sh.nb * tiles_per_unit < 4LL * resident) g += 8;
   return (int)(g < heads ? g : heads);
 }
