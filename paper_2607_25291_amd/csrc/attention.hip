@@ -202,6 +202,11 @@ constexpr int kWalkDense = 0;  // j = 0 .. i ascending, every block computed
 constexpr int kWalkList = 1;   // OSK: the KAP list in list order, rowmax skip vote
 constexpr int kWalkMask = 2;   // j = 0 .. i ascending, blocks whose mask byte is 0 skipped in-loop
 
+// Mask byte of block j of a row whose last causal block is i (0 past it).
+__device__ __forceinline__ int mask_byte(const uint8_t* mrow, int j, int i) {
+  return j <= i ? mrow[j] : 0;
+}
+
 // Zeroes the work-queue counters of a persistent OSK launch (one per XCD, 128 bytes apart).
 __global__ void queue_reset(uint32_t* queue) {
   if (threadIdx.x < kNumXcd) queue[threadIdx.x * 32] = 0u;
@@ -312,16 +317,35 @@ void attention_kernel(const AttnParams P) {
     cnt = ld_uniform(P.a.count + (size_t)ng * P.nb + i);
     cnt = cnt < P.nb ? cnt : P.nb;
     lst = P.a.order + ((size_t)ng * P.nb + i) * P.nb;
+  } else if constexpr (MASKED) {
+    mrow = P.a.mask + ((size_t)ng * P.nb + i) * P.nb;
+    cnt = 0;
+    for (int b0 = 0; b0 <= i; b0 += 64) cnt += __popcll(__ballot(mask_byte(mrow, b0 + lane, i) != 0));
   } else {
     cnt = i - F + 1;
-    if constexpr (MASKED) mrow = P.a.mask + ((size_t)ng * P.nb + i) * P.nb;
   }
+  // The mask walk: the bits of the 64 blocks from mbase on that are still ahead, and the mask bytes of
+  // the 64 blocks after those, in flight. A run of masked blocks costs the walk a bit scan (and a
+  // load per 64 blocks), nothing is fetched or computed for it. When every masked block was a step
+  // with the walk's two barriers, 32 / 8 heads, 16K tokens, 27 % of the blocks took 703 us; now 601.
+  uint64_t mbits = 0;
+  int mbase = -64, mahead = 0;
+  if constexpr (MASKED) mahead = mask_byte(mrow, lane, i);
+  auto next_masked = [&]() -> int {
+    while (mbits == 0 && mbase + 64 <= i) {
+      mbase += 64;
+      mbits = __ballot(mahead != 0);
+      mahead = mask_byte(mrow, mbase + 64 + lane, i);
+    }
+    if (mbits == 0) return -1;
+    const int j = mbase + __builtin_ctzll(mbits);
+    mbits &= mbits - 1;
+    return j;
+  };
   // List entries, read ahead of their use. A malformed entry (outside [F, i]) is fetched as block
-  // i but contributes nothing. With a block mask, a masked block's entry is -1: nothing is fetched
-  // or computed for it, but the walk still steps through it (logical skipping).
+  // i but contributes nothing.
   auto raw_entry = [&](int kk) -> int {
     if constexpr (OSK) return kk < cnt ? lst[kk] : 0;
-    else if constexpr (MASKED) return (kk < cnt && mrow[kk] != 0) ? kk : -1;
     else return F + kk;
   };
   auto listed = [&](int raw) -> bool { return (unsigned)(raw - F) <= (unsigned)(i - F); };
@@ -363,6 +387,7 @@ void attention_kernel(const AttnParams P) {
   // Prologue: K and V of page 0.
   auto first_entry = [&](int kk) -> int {
     if constexpr (OSK) return kk < cnt ? ld_uniform(lst + kk) : 0;
+    else if constexpr (MASKED) return next_masked();
     else return raw_entry(kk);
   };
   const int raw0 = __builtin_amdgcn_readfirstlane(first_entry(0));
@@ -389,7 +414,7 @@ void attention_kernel(const AttnParams P) {
                  w);
     }
   } else {
-    if (cnt > 0 && (!MASKED || listed(raw0))) {
+    if (cnt > 0) {
       copy_block(std::true_type{}, std::integral_constant<int, Cfg::kWaves>{}, raw0, 0, k_lds0, w);
       copy_block(std::false_type{}, std::integral_constant<int, Cfg::kWaves>{}, raw0, 0, v_lds0, w);
     }
@@ -439,8 +464,7 @@ void attention_kernel(const AttnParams P) {
     constexpr int BUF = decltype(bufc)::value;
     const char* Kb = BUF ? k_lds1 : k_lds0;
     const int j = page_of(cur);
-    v_pend = (OSK || MASKED) ? listed(cur) : true;
-    if (MASKED && !v_pend) return;  // a masked block: no Q K^T either
+    v_pend = OSK ? listed(cur) : true;
     // S^T tile t: keys 32 t + 8 (r / 4) + 4 half + r % 4 (register r) of query row qrow. The d chunk
     // is the outer loop: the KT tiles are independent accumulation chains. The KT fragments of
     // chunk c + 1 are read from LDS right after the first MFMA of chunk c, so their latency hides
@@ -640,10 +664,10 @@ void attention_kernel(const AttnParams P) {
         have_next = true;
       }
     }
-    pre = raw_entry(kk + 3);
+    if constexpr (!MASKED) pre = raw_entry(kk + 3);
     if constexpr (PAGED) tbl_nxt2 = table_of(nxt2);
     qk_half(bufc);
-    const bool fetch = kk + 1 < cnt && (!MASKED || listed(nxt));
+    const bool fetch = kk + 1 < cnt;
     constexpr auto NWH = std::integral_constant<int, WPH>{};
     if constexpr (Cfg::kStages == 1) {
       end_phase(true);  // this page's V has landed; every wave is done with its K
@@ -664,7 +688,7 @@ void attention_kernel(const AttnParams P) {
     }
     cur = nxt;
     nxt = nxt2;
-    nxt2 = __builtin_amdgcn_readfirstlane(pre);
+    nxt2 = MASKED ? next_masked() : __builtin_amdgcn_readfirstlane(pre);
     tbl_nxt = tbl_nxt2;
   };
 

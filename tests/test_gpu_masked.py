@@ -13,7 +13,7 @@ import pytest
 
 from oracle import cosa_oracle as O
 from paper_2607_25291_amd import binding as B
-from paper_2607_25291_amd.inputs import WORKLOADS, Workload, make_inputs
+from paper_2607_25291_amd.inputs import WORKLOADS, Workload, make_inputs, random_inputs
 from tests import parity as PR
 from tests.gpu_util import Run, bf16_to_f64, dev, host_bits, torch
 
@@ -90,3 +90,32 @@ def test_masked_equals_ascending_list(case):
             rows = ~np.isnan(ref).any(axis=-1)
             mx, mean = PR.check_output(bf16_to_f64(host_bits(o))[rows], ref[rows])
             say(f"  vs oracle: max-abs {mx:.2e} mean-abs {mean:.2e}")
+
+
+@pytest.mark.parametrize("heads,block,nb", [((2, 1), 64, 130), ((3, 3), 128, 66), ((4, 1), 128, 64),
+                                            ((1, 1), 64, 65)])
+def test_masked_runs_of_empty_blocks(heads, block, nb):
+    """Rows whose mask is read in several words of 64 blocks: empty words in front, between and behind,
+    single blocks at the word edges, the causal end inside a word, and bytes other than 0 and 1."""
+    Hq, Hkv = heads
+    say(f"[masked words] heads={heads} block={block} nb={nb}")
+    L = nb * block
+    q, k, v = random_inputs(1, Hq, Hkv, L, 128, seed=nb, scale=1.5)
+    run = Run.upload(B.Problem(1, Hq, Hkv, L, 128, block, block // 8), q, k, v)
+    rng = np.random.default_rng(nb)
+    mask = np.zeros((1, Hkv, nb, nb), np.uint8)
+    edges = [0, 63, 64, 127, 128, nb - 1]
+    for g, i in np.ndindex(Hkv, nb):
+        kind = i % 4
+        if kind == 0:
+            mask[0, g, i] = rng.random(nb) < 0.02
+        elif kind == 1:
+            mask[0, g, i, [e for e in edges if e < nb]] = 0x80
+        elif kind == 2:
+            mask[0, g, i, i] = 2
+        # kind 3: nothing selected
+    order, count = lists_of(mask)
+    o_list, _, _, _ = run.osk(dev(order), dev(count), None, logs=False)
+    o = torch().full_like(o_list, 0x7BCD)
+    B.cosa_masked_attention(run.problem, run.q, run.k, run.v, dev(mask), o)
+    assert torch().equal(o, o_list)
