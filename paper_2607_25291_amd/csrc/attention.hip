@@ -209,7 +209,7 @@ __device__ __forceinline__ int mask_byte(const uint8_t* mrow, int j, int i) {
 
 // Zeroes the work-queue counters of a persistent OSK launch (one per XCD, 128 bytes apart).
 __global__ void queue_reset(uint32_t* queue) {
-  if (threadIdx.x < kNumXcd) queue[threadIdx.x * 32] = 0u;
+  if (threadIdx.x < kNumXcd) queue[threadIdx.x * kOskQueueStep] = 0u;
 }
 
 template <int BLOCK, int HPW, int WALK, int PG, bool PERSIST>
@@ -248,7 +248,7 @@ void attention_kernel(const AttnParams P) {
   bool have_next = false;
   auto claim = [&]() -> int {
     while (qtried < kNumXcd) {
-      const int p = qx + kNumXcd * (int)atomicAdd(&P.a.queue[qx * 32], 1u);
+      const int p = qx + kNumXcd * (int)atomicAdd(&P.a.queue[qx * kOskQueueStep], 1u);
       if (p < n_slots) return p;
       qx = (qx + 1) & (kNumXcd - 1);
       ++qtried;
@@ -660,7 +660,7 @@ void attention_kernel(const AttnParams P) {
     constexpr int BUF = decltype(bufc)::value;
     if constexpr (PERSIST) {
       if (kk == cnt - 1 && threadIdx.x == 0 && qtried < kNumXcd) {
-        k_next = atomicAdd(&P.a.queue[qx * 32], 1u);
+        k_next = atomicAdd(&P.a.queue[qx * kOskQueueStep], 1u);
         have_next = true;
       }
     }
@@ -774,13 +774,15 @@ void launch_t(const Shape& sh, AttnParams& P, int cus, hipStream_t stream) {
   const int resident = cus * Cfg::kWgPerCu;
   P.group_heads = heads_per_group(sh, HPW, resident);
   if constexpr (WALK == kWalkList) {
-    if (P.a.queue != nullptr) {
+    // A queue is of no use to a grid that is resident as a whole.
+    if (P.a.queue != nullptr && slots > resident) {
       // As many workgroups as the LDS footprint admits, fed by the work queues: one per CU for head
       // pairs of b = 128, two for pairs of b = 64 (packed 25K tokens, 16 / 4 heads: 288 -> 230 us
       // against one).
-      hipLaunchKernelGGL(queue_reset, dim3(1), dim3(64), 0, stream, P.a.queue);
+      if (!P.a.queue_ready)
+        hipLaunchKernelGGL(queue_reset, dim3(1), dim3(64), 0, stream, P.a.queue);
       hipLaunchKernelGGL((attention_kernel<BLOCK, HPW, WALK, PG, true>),
-                         dim3(resident < slots ? resident : slots), dim3(Cfg::kThreads), 0, stream, P);
+                         dim3(resident), dim3(Cfg::kThreads), 0, stream, P);
       return;
     }
   }

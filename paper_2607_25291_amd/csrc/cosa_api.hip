@@ -278,17 +278,18 @@ cosa_status prefill(const cosa_problem* problem, const void* q, const void* k, c
   const hipStream_t s = as_stream(stream);
   hipError_t e = cosa::launch_kap_score(
       sh, cosa::KapScoreArgs{static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), score,
-                             hrm, pg, sp, keys},
+                             hrm, pg, sp, cosa::kap_staging_pays(sh, sp) ? keys : nullptr},
       s);
   if (e != hipSuccess) return hip_fail(e, "kap_score launch");
   e = cosa::launch_kap_select(
       sh,
-      cosa::KapSelectArgs{score, hrm, order, count, (int)select->mode, (int)select->order, micro, sp},
+      cosa::KapSelectArgs{score, hrm, order, count, (int)select->mode, (int)select->order, micro, sp,
+                          queue},
       s);
   if (e != hipSuccess) return hip_fail(e, "kap_select launch");
   cosa::AttnArgs a{static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                    static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), order, count,
-                   nullptr, nullptr, nullptr, on, tau, pg, nullptr, sp, queue};
+                   nullptr, nullptr, nullptr, on, tau, pg, nullptr, sp, queue, true};
   e = cosa::launch_osk_attention(sh, a, s);
   return e == hipSuccess ? ok() : hip_fail(e, "osk_attention launch");
 }

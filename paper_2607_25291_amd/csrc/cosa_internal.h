@@ -66,6 +66,7 @@ struct KapSelectArgs {
   int order_mode;   // cosa_order_mode
   int64_t value_micro;  // budget or p in millionths
   SeqPack pack;
+  uint32_t* queue;      // work-queue counters of the OSK launch that follows, zeroed here, or nullptr
 };
 
 struct AttnArgs {
@@ -84,10 +85,15 @@ struct AttnArgs {
   const uint8_t* mask;    // block mask [B, Hkv, nb, nb] (masked walk only)
   SeqPack pack;           // packed sequences (OSK and dense walks); tau per sequence
   uint32_t* queue;        // OSK: kOskQueueBytes of work-queue counters (persistent grid), or nullptr
+  bool queue_ready;       // the counters are zero already (an earlier kernel of the stream cleared them)
 };
 
 // Work-queue counters of the persistent OSK grid: one 32-bit counter per XCD, 128 bytes apart.
 constexpr size_t kOskQueueBytes = kNumXcd * 128;
+constexpr int kOskQueueStep = 32;  // counters are this many words apart
+
+// Whether cosa_prefill* should stage the sampled keys before scoring (kap_score.hip gives the sizes).
+bool kap_staging_pays(const Shape& sh, const SeqPack& pack);
 
 // LDS bytes the proxy-scoring kernel needs for a shape (0 if the shape is outside its limits).
 size_t kap_score_lds_bytes(const Shape& sh);

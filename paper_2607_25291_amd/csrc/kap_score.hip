@@ -913,6 +913,25 @@ size_t kap_stage_bytes(const Shape& sh) {
   return align256(keys) + (size_t)pair_grid(sh) * sh.nb * 32 * sizeof(float);
 }
 
+// In place, every unit loads its own keys, 32 scattered rows per load; staging reads them once more
+// and adds a launch, then halves the loads of each pair of units and makes them contiguous. Which
+// wins follows from the 32-key chunks that all units load between them, n (n spb / 32) / 2 per head
+// and sequence of n blocks. In place / staged, us: 32 / 8 heads, 8 samples, 16 blocks (256 chunks)
+// 7.0 / 11.8, 64 (4096) 12.1 / 13.1, 96 (9216) 19.7 / 18.4, 128 (16384) 28.3 / 20.4; 16 samples, 48
+// blocks (4608) 19.5 / 19.9, 64 (8192) 23.4 / 21.7; 4 samples, 96 blocks (4608) 13.2 / 16.7, 128 (8192)
+// 18.8 / 18.0; 16 / 16 heads, 64 blocks (8192) 17.0 / 17.6, 97 (18816) 31.2 / 28.4.
+bool kap_staging_pays(const Shape& sh, const SeqPack& pack) {
+  long long sq = (long long)sh.nb * sh.nb;
+  if (pack.n > 0) {
+    sq = 0;
+    for (int q = 0; q < pack.n; ++q) {
+      const long long n = pack.cu[q + 1] - pack.cu[q];
+      sq += n * n;
+    }
+  }
+  return (long long)sh.B * sh.Hkv * sq * sh.spb / 64 > 5000;
+}
+
 size_t kap_score_lds_bytes(const Shape& sh) {
   const int R = sh.G * sh.spb;
   if (R > 128) return 0;

@@ -118,3 +118,54 @@ def test_packed_tiles(lens, heads, block):
                           nbytes, op)
     ref = O.dense_attention_varlen(q, k, v, cu, block=block)
     PR.check_output(bf16_to_f64(host_bits(op)), ref)
+
+
+@pytest.mark.parametrize("heads,block,nb,mode,lens", [
+    # keys in place; the grid resident as a whole (no queue), then fed by queues
+    ((2, 2), 128, 5, B.SELECT_FRACTION, None), ((32, 8), 128, 40, B.SELECT_FRACTION, None),
+    ((16, 4), 64, 130, B.SELECT_TOP_P, None), ((8, 2), 64, 60, B.SELECT_ALL, (20, 1, 39)),
+    # the block counts on either side of the staging threshold (8 heads: 70 and 71), 64-token blocks
+    ((16, 8), 64, 70, B.SELECT_FRACTION, None), ((16, 8), 64, 71, B.SELECT_FRACTION, None),
+    ((24, 8), 64, 90, B.SELECT_FRACTION, (40, 50)),
+])
+def test_prefill_equals_stages(heads, block, nb, mode, lens):
+    """cosa_prefill on a workspace full of stale bytes (the work-queue counters among them), twice in
+    a row, against its stages called one by one."""
+    Hq, Hkv = heads
+    say(f"[prefill stages] heads={heads} block={block} nb={nb} mode={mode} lens={lens}")
+    L = nb * block
+    q, k, v = random_inputs(1, Hq, Hkv, L, 128, seed=nb, scale=1.5)
+    p = B.Problem(1, Hq, Hkv, L, 128, block, block // 8)
+    run = Run.upload(p, q, k, v)
+    t = torch()
+    sel = B.select(mode, 0.4)
+    sk = B.skip(B.SKIP_ROWMAX, (min(lens) if lens else nb) * block * 0.5)
+    order = t.zeros((1, Hkv, nb, nb), dtype=t.int32, device="cuda")
+    count = t.zeros((1, Hkv, nb), dtype=t.int32, device="cuda")
+    score = t.zeros((1, Hkv, nb, nb), dtype=t.float32, device="cuda")
+    hrm = t.zeros((1, Hkv, nb, nb), dtype=t.uint8, device="cuda")
+    o, o2 = t.zeros_like(run.q), t.zeros_like(run.q)
+    nbytes = B.cosa_prefill_workspace_bytes(p)
+    ws = t.full((nbytes,), 0xFF, dtype=t.uint8, device="cuda")
+    if lens:
+        vl = B.varlen(np.concatenate([[0], np.cumsum(lens)]).tolist())
+        B.cosa_kap_score_varlen(p, vl, run.q, run.k, score, hrm)
+        B.cosa_kap_select_ordered_varlen(p, vl, score, hrm, sel, order, count)
+        B.cosa_osk_attention_varlen(p, vl, run.q, run.k, run.v, order, count, sk, o)
+    else:
+        B.cosa_kap_score(p, run.q, run.k, score, hrm)
+        B.cosa_kap_select_ordered(p, score, hrm, sel, order, count)
+        B.cosa_osk_attention(p, run.q, run.k, run.v, order, count, sk, o)
+    lay = B.cosa_prefill_workspace_layout(p)
+    for rep in range(2):
+        if lens:
+            B.cosa_prefill_varlen(p, vl, run.q, run.k, run.v, sel, sk, ws, nbytes, o2)
+        else:
+            B.cosa_prefill(p, run.q, run.k, run.v, sel, sk, ws, nbytes, o2)
+        got = ws[lay.order:lay.order + 4 * order.numel()].view(t.int32).view(order.shape)
+        assert t.equal(got, order), rep
+        if not lens:
+            got = ws[lay.score:lay.score + 4 * order.numel()].view(t.float32).view(order.shape)
+            assert t.equal(got.tril(), score.tril()), rep
+        assert t.equal(o, o2), rep
+        o2.fill_(0x7BCD)
