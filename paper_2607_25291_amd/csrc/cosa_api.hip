@@ -276,16 +276,16 @@ cosa_status prefill(const cosa_problem* problem, const void* q, const void* k, c
   uint16_t* keys = reinterpret_cast<uint16_t*>(ws + l.keys);
   uint32_t* queue = reinterpret_cast<uint32_t*>(ws + l.queue);
   const hipStream_t s = as_stream(stream);
-  hipError_t e = cosa::launch_kap_score(
-      sh, cosa::KapScoreArgs{static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), score,
-                             hrm, pg, sp, cosa::kap_staging_pays(sh, sp) ? keys : nullptr},
-      s);
+  const cosa::KapSelectArgs sa{score, hrm, order, count, (int)select->mode, (int)select->order, micro, sp,
+                               queue};
+  cosa::KapScoreArgs ka{static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), score, hrm, pg,
+                        sp, cosa::kap_staging_pays(sh, sp) ? keys : nullptr};
+  const bool fused = ka.kstage == nullptr && cosa::kap_fused_select(sh, sa, ka.sel);
+  if (!fused) ka.sel = cosa::RowSelect{};
+  ka.queue = queue;
+  hipError_t e = cosa::launch_kap_score(sh, ka, s);
   if (e != hipSuccess) return hip_fail(e, "kap_score launch");
-  e = cosa::launch_kap_select(
-      sh,
-      cosa::KapSelectArgs{score, hrm, order, count, (int)select->mode, (int)select->order, micro, sp,
-                          queue},
-      s);
+  if (!fused) e = cosa::launch_kap_select(sh, sa, s);
   if (e != hipSuccess) return hip_fail(e, "kap_select launch");
   cosa::AttnArgs a{static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                    static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), order, count,

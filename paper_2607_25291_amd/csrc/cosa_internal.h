@@ -47,6 +47,17 @@ struct PackOrder {
   int start[kMaxPackedSeqs];
 };
 
+// The fraction cut as one wavefront per row takes it (select_wave.h).
+struct RowSelect {
+  const float* score;
+  const uint8_t* hrm;
+  int32_t* order;       // nullptr: no selection
+  int32_t* count;
+  int order_mode;       // cosa_order_mode
+  int k2max;            // kept keys of the longest row, rounded up to a power of two
+  int64_t value_micro;  // budget in millionths
+};
+
 struct KapScoreArgs {
   const uint16_t* q;
   const uint16_t* k;   // contiguous K, or the paged K cache
@@ -55,6 +66,8 @@ struct KapScoreArgs {
   KvPages pg;
   SeqPack pack;
   uint16_t* kstage;    // kap_stage_bytes() of scratch for the staged sampled keys, or nullptr
+  RowSelect sel;       // in place only: the row's selection by the workgroup that scored it
+  uint32_t* queue;     // with sel: cleared as by KapSelectArgs
 };
 
 struct KapSelectArgs {
@@ -94,6 +107,9 @@ constexpr int kOskQueueStep = 32;  // counters are this many words apart
 
 // Whether cosa_prefill* should stage the sampled keys before scoring (kap_score.hip gives the sizes).
 bool kap_staging_pays(const Shape& sh, const SeqPack& pack);
+
+// Whether the in-place scoring kernel can also take this selection, and its description if so.
+bool kap_fused_select(const Shape& sh, const KapSelectArgs& a, RowSelect& sel);
 
 // LDS bytes the proxy-scoring kernel needs for a shape (0 if the shape is outside its limits).
 size_t kap_score_lds_bytes(const Shape& sh);

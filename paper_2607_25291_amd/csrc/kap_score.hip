@@ -23,6 +23,7 @@
 
 #include "cosa_device.h"
 #include "cosa_internal.h"
+#include "select_wave.h"
 
 namespace cosa {
 namespace {
@@ -342,9 +343,11 @@ __device__ __forceinline__ void score_column(int R, const float* mu, const float
 }
 
 // One unit per workgroup. STAGED: the sampled keys come from the staged copy (P.a.kstage).
-template <int SPB, int RT, bool PAGED, bool STAGED>
+// SELECT: the row's fraction cut follows on the workgroup's first wavefront, in the block maxima's LDS
+// (small problems, whose selection as a kernel of its own is mostly the launch).
+template <int SPB, int RT, bool PAGED, bool STAGED, bool SELECT>
 __global__ __launch_bounds__(kScoreThreads) void kap_score_kernel(const KapParams P) {
-  extern __shared__ float beta[];  // [R][nbp]
+  extern __shared__ __attribute__((aligned(16))) float beta[];  // [R][nbp]
   __shared__ float mu[RT * 32], mu2[RT * 32];
   __shared__ float wmax[kScoreWaves][RT * 32];  // each wave's row maxima
 
@@ -407,6 +410,12 @@ __global__ __launch_bounds__(kScoreThreads) void kap_score_kernel(const KapParam
 #pragma unroll
       for (int r = 0; r < 4; ++r) b[r] = beta[(row + r) * P.nbp + j];
     }, srow[j], hrow[j]);
+  if constexpr (SELECT) {
+    clear_queue(P.a.queue);
+    __syncthreads();  // the row's scores are written, its block maxima no longer read
+    if (w == 0)
+      select_row_wave<kFusedPerLane>(P.a.sel, P.nb, ng, F, i, lane, reinterpret_cast<uint64_t*>(beta));
+  }
 }
 
 // Work items of kap_pair_kernel: item q is KV head ng, pair k (units nb-1-2k and nb-2-2k). When the
@@ -827,24 +836,28 @@ hipError_t allow_lds(const void* fn, size_t lds, std::mutex& mu, size_t& granted
   return hipSuccess;
 }
 
-template <int SPB, int RT, bool PAGED, bool STAGED>
+template <int SPB, int RT, bool PAGED, bool STAGED, bool SELECT>
 hipError_t launch_t(const KapParams& P, size_t lds, hipStream_t stream) {
   static std::mutex mu;
   static size_t granted = 0;
+  if constexpr (SELECT) {
+    const size_t need = (size_t)select_wave_keys(P.a.sel.k2max) * sizeof(uint64_t);
+    lds = lds > need ? lds : need;
+  }
   const hipError_t e = allow_lds(
-      reinterpret_cast<const void*>(&kap_score_kernel<SPB, RT, PAGED, STAGED>), lds, mu, granted);
+      reinterpret_cast<const void*>(&kap_score_kernel<SPB, RT, PAGED, STAGED, SELECT>), lds, mu, granted);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((kap_score_kernel<SPB, RT, PAGED, STAGED>),
+  hipLaunchKernelGGL((kap_score_kernel<SPB, RT, PAGED, STAGED, SELECT>),
                      dim3(proxy_slots(P.n_units / P.nb, P.nb)), dim3(kScoreThreads), lds, stream, P);
   return hipGetLastError();
 }
 
-template <int SPB, bool PAGED, bool STAGED>
+template <int SPB, bool PAGED, bool STAGED, bool SELECT = false>
 hipError_t launch_rt(const KapParams& P, size_t lds, hipStream_t stream) {
   const int rt = (P.R + 31) / 32;
-  if (rt <= 1) return launch_t<SPB, 1, PAGED, STAGED>(P, lds, stream);
-  if (rt <= 2) return launch_t<SPB, 2, PAGED, STAGED>(P, lds, stream);
-  return launch_t<SPB, 4, PAGED, STAGED>(P, lds, stream);
+  if (rt <= 1) return launch_t<SPB, 1, PAGED, STAGED, SELECT>(P, lds, stream);
+  if (rt <= 2) return launch_t<SPB, 2, PAGED, STAGED, SELECT>(P, lds, stream);
+  return launch_t<SPB, 4, PAGED, STAGED, SELECT>(P, lds, stream);
 }
 
 // Persistent grid of kap_pair_kernel: a multiple of 8 workgroups, at most one per CU.
@@ -899,6 +912,10 @@ hipError_t launch_spb(const Shape& sh, KapParams& P, size_t lds, hipStream_t str
       return launch_pair<SPB>(P, pair_grid(sh), pair_lds_bytes(sh), stream);
     }
     return launch_rt<SPB, false, true>(P, lds, stream);
+  }
+  if (P.a.sel.order != nullptr) {
+    if (P.a.pg.table != nullptr) return launch_rt<SPB, true, false, true>(P, lds, stream);
+    return launch_rt<SPB, false, false, true>(P, lds, stream);
   }
   if (P.a.pg.table != nullptr) return launch_rt<SPB, true, false>(P, lds, stream);
   return launch_rt<SPB, false, false>(P, lds, stream);
