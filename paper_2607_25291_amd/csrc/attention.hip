@@ -12,7 +12,7 @@
 // spent on staging), double-buffered. Each wave works through its pages in two halves,
 //   QK(m): Q K^T of page m, the diagonal mask, the new running max and the wave's skip vote;
 //   PV(m): the skip decision from the votes, softmax, P V of page m;
-// with a workgroup barrier after each half. With two heads in a workgroup the waves of the second
+// with a workgroup barrier after each half. With two heads of 128-row tiles the waves of the second
 // head start one barrier later, so phase 2m runs QK(m) of head 0 beside PV(m-1) of head 1 and phase
 // 2m+1 runs PV(m) of head 0 beside QK(m) of head 1. Waves w and w + 4 share a SIMD: while one
 // issues the Q K^T MFMAs the other runs its softmax VALU work and P V MFMAs. The waves of head 0
@@ -692,7 +692,12 @@ void attention_kernel(const AttnParams P) {
     tbl_nxt = tbl_nxt2;
   };
 
-  if (HPW == 2 && hw == 1) end_phase(false);  // head slot 1 runs one phase behind
+  // With b = 128 the two heads' waves share SIMDs and head slot 1 runs one phase behind. With b = 64
+  // they sit on different SIMDs, and it is another workgroup's wave that fills a SIMD's gaps: there
+  // both heads run the same phase, so that a Q K^T half does not wait for the partner's P V (packed
+  // 25K tokens, 16 / 4 heads 209.5 -> 203.6 us; 32 / 8 heads, 16K tokens 544 -> 520 us).
+  constexpr bool STAGGER = HPW == 2 && BLOCK == 128;
+  if (STAGGER && hw == 1) end_phase(false);
   if constexpr (Cfg::kStages == 1) {
     for (int kk = 0; kk < cnt; ++kk) page(kk, std::integral_constant<int, 0>{});
   } else {
@@ -701,7 +706,7 @@ void attention_kernel(const AttnParams P) {
       if (kk + 1 < cnt) page(kk + 1, std::integral_constant<int, 1>{});
     }
   }
-  if (HPW == 2 && hw == 0) end_phase(false);  // same barrier count for both head slots
+  if (STAGGER && hw == 0) end_phase(false);  // same barrier count for both head slots
 
   lsum = half_sum(lsum);
   const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
