@@ -795,15 +795,18 @@ void launch_t(const Shape& sh, AttnParams& P, int cus, hipStream_t stream) {
                      dim3(Cfg::kThreads), 0, stream, P);
 }
 
-// Two heads per workgroup where the group size is even, unless there are so few tiles that a pair of
-// heads per CU or less is all there is: single heads then spread over the CUs, and a head's walk does
-// not wait for its partner's (dense, 4 / 1 heads, 8K tokens: 168 -> 135 us; prefill 32 / 8 heads, 2K
-// tokens 43 -> 40 us). Dense tiles of 64-token blocks keep the pairs (72 against 75 us at 4 / 1
-// heads, 4K tokens: their pages are short and the shared fetch counts more).
+// Two heads per workgroup where the group size is even, unless there are few tiles, at most three
+// head pairs for every two CUs: single heads then spread over the CUs more evenly, and a head's walk
+// does not wait for its partner's (pairs / single heads, us: dense, 4 / 1 heads, 8K tokens (128 pairs)
+// 168 / 135; 32 / 8 heads, 17 blocks (272): dense 57.2 / 52.2, masked 40.2 / 36.9, prefill 36.1 / 33.1;
+// 24 blocks (384): 85.4 / 82.0, 53.6 / 50.7, 45.9 / 44.1; 32 blocks (512): prefill 68.0 / 69.3).
+// 64-token blocks: list walks of up to one pair per CU only (dense, 4 / 1 heads, 64 blocks 72 / 75;
+// their pages are short, and fetching them once for both heads counts more).
 template <int WALK, int PG>
 void launch_shape(const Shape& sh, AttnParams& P, hipStream_t stream) {
   const int cus = cu_count();
-  const bool few = (long long)P.n_units * (sh.G / 2) <= cus && (sh.b == 128 || WALK == kWalkList);
+  const long long pairs = (long long)P.n_units * (sh.G / 2);
+  const bool few = sh.b == 128 ? 2 * pairs <= 3 * cus : WALK == kWalkList && pairs <= cus;
   const bool pair = (sh.G % 2) == 0 && !few;
   if (sh.b == 128) {
     if (pair) launch_t<128, 2, WALK, PG>(sh, P, cus, stream);

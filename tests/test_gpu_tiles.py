@@ -34,8 +34,8 @@ CASES = [
     (1, 2, 1, 64, 1), (2, 8, 2, 64, 7),
     # groups of eight heads with a remainder, and heads that do not divide the XCDs
     (1, 9, 9, 64, 6), (3, 6, 3, 128, 4), (1, 17, 17, 128, 3),
-    # the last block count at which even groups run as single heads (256 pairs), and the next one
-    (1, 32, 8, 128, 16), (1, 32, 8, 128, 17),
+    # the last block count at which even groups run as single heads (384 pairs), and the next one
+    (1, 64, 8, 128, 12), (1, 64, 8, 128, 13),
 ]
 
 
