@@ -218,8 +218,8 @@ cosa_status cosa_osk_attention(const cosa_problem* problem, const void* q, const
                                float* margin_log, int32_t* n_computed, void* stream);
 
 /*
- * cosa_osk_attention as cosa_prefill runs it: a persistent grid that fills the compute units and
- * takes (query block, head pair) tiles from eight work queues, one per XCD, heaviest query
+ * cosa_osk_attention as cosa_prefill runs it: where there are more tiles than the compute units hold
+ * at once, a persistent grid that takes (query block, head pair) tiles from eight work queues, one per XCD, heaviest query
  * blocks first; a workgroup drains its own XCD's queue, then the others. Same arguments, results
  * and logs as cosa_osk_attention, bit for bit. queue: device memory of at least
  * cosa_osk_attention_queue_bytes() bytes, 4-byte aligned, owned by the caller; its contents are
@@ -274,9 +274,10 @@ cosa_status cosa_prefill_workspace_layout(const cosa_problem* problem,
                                           cosa_workspace_layout* layout);
 
 /*
- * Complete proxy-kernel workflow (Algorithm A): cosa_kap_score_staged, cosa_kap_select_ordered
- * and cosa_osk_attention enqueued back to back on one stream, with the proxy tensors and the staged
- * keys in the caller-provided workspace (at least cosa_prefill_workspace_bytes(), 16-byte
+ * Complete proxy-kernel workflow (Algorithm A): the work of cosa_kap_score (with the keys staged where
+ * that pays), cosa_kap_select_ordered and cosa_osk_attention enqueued back to back on one stream,
+ * bit-identical to those calls, with the proxy tensors and the staged keys in the caller-provided
+ * workspace (at least cosa_prefill_workspace_bytes(), 16-byte
  * aligned; contents on return are the proxy tensors at cosa_prefill_workspace_layout() offsets).
  * skip may be NULL.
  */

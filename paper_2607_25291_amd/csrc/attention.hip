@@ -23,7 +23,7 @@
 // of delaying the Q K^T chain. A wave waits for its own copies at the end of its PV half, so every
 // copy has the rest of its phase and the next one to land before the barrier that publishes it.
 //
-// With one head in a workgroup (an odd number of query heads per KV head) nothing inside the workgroup
+// With one head in a workgroup (an odd number of query heads per KV head, or few tiles) nothing inside the workgroup
 // fills the other's waits, so it keeps one page buffer per tensor instead of two and several
 // workgroups share a CU (two of b = 128, four of b = 64: two waves per SIMD again), each at its own
 // point of the walk. The next K page is fetched during PV(m) and the next V page during QK(m+1).
@@ -32,8 +32,9 @@
 // fetch each page once for both heads (32 / 8 heads, 32K tokens: 5 % faster than single heads).
 //
 // The grid is either one workgroup per tile (query block, head pair) or, when the caller supplies
-// work-queue counters, persistent: as many workgroups as the CUs hold take tiles from per-XCD queues in the
-// order the hardware would run them (see the tile loop below).
+// work-queue counters and the tiles outnumber what the CUs hold at once, persistent: as many workgroups
+// as the CUs hold take tiles from per-XCD queues in the order the hardware would run them (see the
+// tile loop below). The order of the tiles is unit_tile's, the choice of heads launch_shape's.
 // With a paged KV cache (Sec. 4.3 "Physical jumping over pages"; appendix D.1) the copies gather a
 // block's rows through the page table; everything from the LDS layouts on is shared.
 //

@@ -276,8 +276,8 @@ cosa_status prefill(const cosa_problem* problem, const void* q, const void* k, c
   uint16_t* keys = reinterpret_cast<uint16_t*>(ws + l.keys);
   uint32_t* queue = reinterpret_cast<uint32_t*>(ws + l.queue);
   const hipStream_t s = as_stream(stream);
-  const cosa::KapSelectArgs sa{score, hrm, order, count, (int)select->mode, (int)select->order, micro, sp,
-                               queue};
+  const cosa::KapSelectArgs sa{score, hrm,   order, count, (int)select->mode, (int)select->order,
+                               micro, sp,    queue};
   cosa::KapScoreArgs ka{static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), score, hrm, pg,
                         sp, cosa::kap_staging_pays(sh, sp) ? keys : nullptr};
   const bool fused = ka.kstage == nullptr && cosa::kap_fused_select(sh, sa, ka.sel);

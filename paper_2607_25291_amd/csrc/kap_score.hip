@@ -16,7 +16,8 @@
 //     query blocks of one KV head at a time, so that every key fragment loaded into registers
 //     feeds two MFMA tiles (64 rows). The first unit's block maxima live in LDS, the second's in a
 //     per-workgroup scratch in global memory (written and read once per item).
-//   - kap_score_kernel (every other case): one workgroup per unit, block maxima in LDS.
+//   - kap_score_kernel (every other case): one workgroup per unit, block maxima in LDS; in small
+//     prefills the same workgroup then takes the row's selection.
 // Both place work so that each XCD serves as few KV heads as possible (their sampled keys then stay
 // in that XCD's L2), heaviest query blocks first.
 #include <mutex>
