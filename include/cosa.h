@@ -219,9 +219,9 @@ cosa_status cosa_osk_attention(const cosa_problem* problem, const void* q, const
 
 /*
  * cosa_osk_attention as cosa_prefill runs it: where there are more tiles than the compute units hold
- * at once, a persistent grid that takes (query block, head pair) tiles from eight work queues, one per XCD, heaviest query
- * blocks first; a workgroup drains its own XCD's queue, then the others. Same arguments, results
- * and logs as cosa_osk_attention, bit for bit. queue: device memory of at least
+ * at once, a persistent grid that takes (query block, head pair) tiles from eight work queues, one
+ * per XCD, heaviest query blocks first; a workgroup drains its own XCD's queue, then the others. Same
+ * arguments, results and logs as cosa_osk_attention, bit for bit. queue: device memory of at least
  * cosa_osk_attention_queue_bytes() bytes, 4-byte aligned, owned by the caller; its contents are
  * scratch (reset by the call on the stream, meaningless on return), so calls that may run at the
  * same time need distinct queue buffers. Returns COSA_ERR_WORKSPACE if queue is NULL or too small.
