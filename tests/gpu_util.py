@@ -102,3 +102,22 @@ class Run:
 
 def tau_of(delta: float, L: int) -> float:
     return float(np.float32(math.log(float(np.float32(delta)) / L)))
+
+
+# What a call leaves behind shows which kernels it ran.
+
+def queue_left(problem: B.Problem, heads_per_wg: int) -> int:
+    """Value of every work-queue counter after a persistent list walk with `heads_per_wg` heads per
+    workgroup: the slots a queue hands out, and one failed claim of every workgroup."""
+    cus = torch().cuda.get_device_properties(0).multi_processor_count
+    per_cu = {(128, 2): 1, (128, 1): 2, (64, 2): 2, (64, 1): 4}[problem.block, heads_per_wg]
+    units = problem.batch * problem.n_kv_heads * problem.n_blocks
+    G = problem.n_q_heads // problem.n_kv_heads
+    slots = -(-units // 8) * 8 * (G // heads_per_wg)
+    assert slots > cus * per_cu, "the grid is resident as a whole: no queue"
+    return slots // 8 + cus * per_cu
+
+
+def queue_counters(queue):
+    """The eight counters of a work-queue buffer (one per 128 bytes)."""
+    return queue.view(torch().int32)[::32].tolist()

@@ -1,12 +1,14 @@
 """Persistent OSK with work queues: cosa_osk_attention_queued must equal cosa_osk_attention bit for bit.
 
-The queued launch runs the same tile code on a grid of one workgroup per compute unit that takes
-(query block, head pair) tiles from per-XCD queues, so every output, log entry and computed count is
-the same as with one workgroup per tile. The cases cover two head slots per workgroup (b = 128 and
-b = 64), one head slot (odd group size), batch > 1, a queue buffer holding stale values, repeated
-calls on the same queue, and the 128K shape of the benchmark (skip threshold ln(Delta/L) = -3).
-The oracle parity of the walk itself is covered by the hardware-dispatched path's tests, and
-cosa_prefill, which runs the queued launch, is compared with the stage calls there.
+Where there are more tiles than the compute units hold at once, the queued launch runs the same tile
+code on as many workgroups as they hold, which take (query block, head pair or head) tiles from per-XCD
+queues, so every output, log entry and computed count is the same as with one workgroup per tile. The
+large cases are of that kind (the counters left in the queue buffer show it): head pairs and single
+heads, b = 128 and b = 64, batch > 1, a queue buffer holding stale values, repeated calls on the same
+queue, and the 128K shape of the benchmark (skip threshold ln(Delta/L) = -3). A grid that is resident as a
+whole uses no queue and leaves the buffer alone: the small cases. The oracle parity of the walk itself
+is covered by the hardware-dispatched path's tests, and cosa_prefill, which runs the queued launch, is
+compared with the stage calls there.
 """
 import math
 import sys
@@ -16,7 +18,7 @@ import pytest
 
 from paper_2607_25291_amd import binding as B
 from paper_2607_25291_amd.inputs import WORKLOADS, Workload, make_inputs
-from tests.gpu_util import dev, torch
+from tests.gpu_util import dev, queue_counters, queue_left, torch
 
 pytestmark = pytest.mark.gpu
 
@@ -32,6 +34,11 @@ CASES = [
     Workload("pair_b64", 1, 4, 2, 1536, 128, 64, 8, 0.5, 0.25, 256, 0.02),
     Workload("single_slot_g3", 1, 6, 2, 2048, 128, 128, 16, 0.4, 0.2, 256, 0.02),
     Workload("one_head_full_budget", 1, 1, 1, 1024, 128, 64, 8, 1.0, 0.5, 128, 0.02),
+    # more tiles than the compute units hold
+    Workload("queue_pair_b128_batch2", 2, 8, 2, 6400, 128, 128, 16, 0.3, 0.15, 256, (0.005, 0.03)),
+    Workload("queue_pair_b64", 1, 16, 4, 4224, 128, 64, 8, 0.3, 0.15, 256, 0.02),
+    Workload("queue_single_b128_g3", 2, 6, 2, 5632, 128, 128, 16, 0.3, 0.15, 256, 0.02),
+    Workload("queue_single_b64", 2, 5, 5, 6656, 128, 64, 8, 0.3, 0.15, 256, 0.02),
 ]
 
 
@@ -80,10 +87,14 @@ def test_queued_equals_one_workgroup_per_tile(w):
     sk = B.skip(B.SKIP_ROWMAX, min(w.seq_len * math.exp(tau), float(w.seq_len)))
     ref = walk(p, qd, kd, vd, order, count, sk)
     queue = t.full((B.cosa_osk_attention_queue_bytes(),), 0xFF, dtype=t.uint8, device="cuda")
+    left = -1  # what the buffer held before
+    if w.name.startswith("queue_"):
+        left = queue_left(p, 2 if "pair" in w.name else 1)
     for rep in range(2):  # stale queue contents first, then the counters the first call left
         got = walk(p, qd, kd, vd, order, count, sk, queue)
         for a, g in zip(ref, got):
             assert np.array_equal(a, g), f"call {rep}"
+        assert queue_counters(queue) == [left] * 8
     assert (ref[3] >= 1).all()  # every tile ran (the first listed block is always computed)
     assert (ref[1] == B.VISIT_SKIPPED).any() and (ref[1] == B.VISIT_COMPUTED).any()
 
@@ -107,6 +118,7 @@ def test_queued_equals_one_workgroup_per_tile_full_size():
             queue = t.zeros((B.cosa_osk_attention_queue_bytes(),), dtype=t.uint8, device="cuda")
             B.cosa_osk_attention_queued(p, qd, kd, vd, order, count, sk, o, queue, queue.numel(),
                                         None, None, nco)
+            assert queue_counters(queue) == [queue_left(p, 2)] * 8
         else:
             B.cosa_osk_attention(p, qd, kd, vd, order, count, sk, o, None, None, nco)
         t.cuda.synchronize()
