@@ -4,7 +4,8 @@ through one or more physical pages when the page size differs from the block siz
 The paged entry points read K and V through a page table from a [n_pages, Hkv, page, d] cache. On
 the same data they must give results bit-identical to the contiguous entry points, which the
 oracle parity tests cover; the tiny case is also checked against the oracle directly. Unused pages
-hold random values, so a wrong page lookup cannot go unnoticed.
+hold random values, so a wrong page lookup cannot go unnoticed. The larger cases reach the kernels of
+serving sizes (head pairs, work queues, staged keys); what the workspace holds afterwards shows it.
 """
 import sys
 
@@ -15,7 +16,7 @@ from oracle import cosa_oracle as O
 from paper_2607_25291_amd import binding as B
 from paper_2607_25291_amd.inputs import WORKLOADS, Workload, make_inputs
 from tests import parity as PR
-from tests.gpu_util import Run, bf16_to_f64, dev, host_bits, torch
+from tests.gpu_util import Run, bf16_to_f64, dev, host_bits, queue_counters, queue_left, torch
 
 pytestmark = pytest.mark.gpu
 
@@ -30,6 +31,22 @@ SMALL_GQA = Workload("small_gqa", 2, 8, 2, 2048, 128, 128, 16, 0.25, 0.125, 256,
 # rows then sit deep inside their page).
 CASES = {"tiny_l2k": (WORKLOADS["tiny_l2k"], [16, 64, 256, 2048]),
          "small_gqa": (SMALL_GQA, [16, 128, 512, 2048])}
+# More tiles than the compute units hold, so that cosa_prefill_paged walks them from work queues: heads
+# per workgroup (the third value) 2 and 1, both block sizes. The last value: whether the sampled keys are
+# staged first ("staged" for the kernel of query block pairs, "staged_r64" with 64 rows a query block).
+QUEUED = {
+    "staged": (Workload("staged", 1, 8, 4, 13440, 128, 128, 8, 0.2, 0.1, 256, 0.02),
+               [16, 128], 2, True),
+    "staged_r64": (Workload("staged_r64", 1, 16, 2, 9216, 128, 64, 8, 0.2, 0.1, 256, 0.02),
+                   [32, 512], 2, True),
+    "pair_b64": (Workload("pair_b64", 1, 16, 4, 4224, 128, 64, 8, 0.3, 0.15, 256, 0.02),
+                 [16, 64], 2, False),
+    "single_b128": (Workload("single_b128", 2, 6, 2, 5632, 128, 128, 16, 0.3, 0.15, 256, 0.02),
+                    [64, 512], 1, False),
+    "single_b64": (Workload("single_b64", 2, 5, 5, 6656, 128, 64, 8, 0.3, 0.15, 256, 0.02),
+                   [16, 256], 1, True),
+}
+CASES.update({name: (w, pages) for name, (w, pages, _, _) in QUEUED.items()})
 
 
 def make_paged(k, v, page, extra, seed):
@@ -110,6 +127,13 @@ def test_paged_prefill_bit_exact_and_oracle(case):
         B.cosa_prefill_paged(p, run.q, kv, sel, sk, ws, nbytes, o)
         torch().cuda.synchronize()
         assert torch().equal(o, o_ref)
+        lay = B.cosa_prefill_workspace_layout(p)
+        got = ws[lay.order:lay.order + 4 * order_ref.numel()].view(torch().int32).view(order_ref.shape)
+        assert torch().equal(got, order_ref)
+        if w.name in QUEUED:
+            queue = ws[lay.queue:lay.queue + B.cosa_osk_attention_queue_bytes()]
+            assert queue_counters(queue) == [queue_left(p, QUEUED[w.name][2])] * 8
+            assert bool(ws[lay.keys:lay.queue].any()) == QUEUED[w.name][3]
     if w.name == "tiny_l2k":
         # the paged output against the oracle walking the same lists
         ref = O.osk_attention(case["q"], case["k"], case["v"], order_ref.cpu().numpy(),
