@@ -16,7 +16,9 @@ from oracle import cosa_oracle as O
 from paper_2607_25291_amd import binding as B
 from paper_2607_25291_amd.inputs import random_inputs
 from tests import parity as PR
-from tests.gpu_util import Run, bf16_to_f64, dev, host_bits, tau_of, torch
+from tests.gpu_util import (Run, bf16_to_f64, dev, host_bits, queue_counters, queue_left, tau_of,
+                            torch)
+from tests.test_gpu_paged import make_paged
 
 pytestmark = pytest.mark.gpu
 
@@ -30,7 +32,7 @@ def say(*a):
 CASES = [
     # an odd group size: one head per workgroup, one page buffer (both block sizes, one block up)
     (1, 1, 1, 128, 1), (1, 3, 1, 128, 2), (2, 3, 3, 128, 5), (1, 5, 1, 64, 3), (1, 7, 1, 64, 9),
-    # two heads per workgroup, 64-token blocks: two workgroups per compute unit
+    # even groups of 64-token blocks: single heads in the list walk, head pairs in the others
     (1, 2, 1, 64, 1), (2, 8, 2, 64, 7),
     # groups of eight heads with a remainder, and heads that do not divide the XCDs
     (1, 9, 9, 64, 6), (3, 6, 3, 128, 4), (1, 17, 17, 128, 3),
@@ -120,19 +122,32 @@ def test_packed_tiles(lens, heads, block):
     PR.check_output(bf16_to_f64(host_bits(op)), ref)
 
 
-@pytest.mark.parametrize("heads,block,nb,mode,lens", [
+# heads per workgroup of a list walk from work queues (0: no queue), sampled keys staged first
+@pytest.mark.parametrize("heads,block,nb,mode,lens,page,queued,staged", [
     # keys in place; the grid resident as a whole (no queue), then fed by queues
-    ((2, 2), 128, 5, B.SELECT_FRACTION, None), ((32, 8), 128, 40, B.SELECT_FRACTION, None),
-    ((16, 4), 64, 130, B.SELECT_TOP_P, None), ((8, 2), 64, 60, B.SELECT_ALL, (20, 1, 39)),
+    ((2, 2), 128, 5, B.SELECT_FRACTION, None, 0, 0, False),
+    ((32, 8), 128, 40, B.SELECT_FRACTION, None, 0, 2, False),
+    ((16, 4), 64, 130, B.SELECT_TOP_P, None, 0, 2, True),
+    ((8, 2), 64, 60, B.SELECT_ALL, (20, 1, 39), 0, 0, False),
     # the block counts on either side of the staging threshold (8 heads: 70 and 71), 64-token blocks
-    ((16, 8), 64, 70, B.SELECT_FRACTION, None), ((16, 8), 64, 71, B.SELECT_FRACTION, None),
-    ((24, 8), 64, 90, B.SELECT_FRACTION, (40, 50)),
+    ((16, 8), 64, 70, B.SELECT_FRACTION, None, 0, 2, False),
+    ((16, 8), 64, 71, B.SELECT_FRACTION, None, 0, 2, True),
+    ((24, 8), 64, 90, B.SELECT_FRACTION, (40, 50), 0, 1, False),
+    # packed and staged: an odd number of blocks, pairs of query blocks across two sequences, key chunks
+    # in front of a sequence; single heads, head pairs and pages
+    ((24, 8), 64, 99, B.SELECT_FRACTION, (65, 31, 1, 2), 0, 1, True),
+    ((16, 8), 64, 99, B.SELECT_FRACTION, (2, 63, 1, 33), 0, 2, True),
+    ((16, 8), 64, 99, B.SELECT_FRACTION, (2, 63, 1, 33), 32, 2, True),
+    ((8, 8), 128, 99, B.SELECT_TOP_P, (2, 63, 34), 128, 1, True),
+    # packed and in place, from pages
+    ((8, 8), 128, 75, B.SELECT_FRACTION, (3, 60, 12), 16, 1, False),
 ])
-def test_prefill_equals_stages(heads, block, nb, mode, lens):
+def test_prefill_equals_stages(heads, block, nb, mode, lens, page, queued, staged):
     """cosa_prefill on a workspace full of stale bytes (the work-queue counters among them), twice in
-    a row, against its stages called one by one."""
+    a row, against its stages called one by one on contiguous keys and values. The work-queue counters
+    and the space of the staged keys show which kernels ran."""
     Hq, Hkv = heads
-    say(f"[prefill stages] heads={heads} block={block} nb={nb} mode={mode} lens={lens}")
+    say(f"[prefill stages] heads={heads} block={block} nb={nb} mode={mode} lens={lens} page={page}")
     L = nb * block
     q, k, v = random_inputs(1, Hq, Hkv, L, 128, seed=nb, scale=1.5)
     p = B.Problem(1, Hq, Hkv, L, 128, block, block // 8)
@@ -156,16 +171,32 @@ def test_prefill_equals_stages(heads, block, nb, mode, lens):
         B.cosa_kap_score(p, run.q, run.k, score, hrm)
         B.cosa_kap_select_ordered(p, score, hrm, sel, order, count)
         B.cosa_osk_attention(p, run.q, run.k, run.v, order, count, sk, o)
+    own = t.ones((nb, nb), dtype=t.bool, device="cuda").tril()  # the entries that are scored
+    if lens:
+        seq = t.repeat_interleave(t.arange(len(lens)), t.tensor(lens)).cuda()
+        own &= seq[:, None] == seq[None, :]
+    if page:
+        kc, vc, table, n_pages = make_paged(k, v, page, 3, nb)
+        cache = [dev(x) for x in (kc, vc, table)]
+        kv = B.paged_kv(*cache, page, n_pages)
     lay = B.cosa_prefill_workspace_layout(p)
     for rep in range(2):
-        if lens:
+        if lens and page:
+            B.cosa_prefill_paged_varlen(p, vl, run.q, kv, sel, sk, ws, nbytes, o2)
+        elif lens:
             B.cosa_prefill_varlen(p, vl, run.q, run.k, run.v, sel, sk, ws, nbytes, o2)
         else:
             B.cosa_prefill(p, run.q, run.k, run.v, sel, sk, ws, nbytes, o2)
         got = ws[lay.order:lay.order + 4 * order.numel()].view(t.int32).view(order.shape)
         assert t.equal(got, order), rep
-        if not lens:
-            got = ws[lay.score:lay.score + 4 * order.numel()].view(t.float32).view(order.shape)
-            assert t.equal(got.tril(), score.tril()), rep
+        got = ws[lay.count:lay.count + 4 * count.numel()].view(t.int32).view(count.shape)
+        assert t.equal(got, count), rep
+        got = ws[lay.score:lay.score + 4 * score.numel()].view(t.float32).view(score.shape)
+        assert t.equal(got[..., own], score[..., own]), rep
+        got = ws[lay.hrm:lay.hrm + hrm.numel()].view(hrm.shape)
+        assert t.equal(got[..., own], hrm[..., own]), rep
         assert t.equal(o, o2), rep
         o2.fill_(0x7BCD)
+    queue = ws[lay.queue:lay.queue + B.cosa_osk_attention_queue_bytes()]
+    assert queue_counters(queue) == [queue_left(p, queued) if queued else 0] * 8
+    assert bool((ws[lay.keys:lay.queue] != 0xFF).any()) == staged
