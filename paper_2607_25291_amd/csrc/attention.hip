@@ -47,6 +47,8 @@
 //               for k = 0..3, element i % 4 of the 8 bytes addressed by lane 4k + i / 4. Lane i
 //               addressing V[key0 + i/4][d0 + 4 (i%4)] therefore receives keys key0..key0+3 of
 //               column d0 + i, which is the P^T key set that lane holds from the S^T accumulators.
+#include <limits.h>
+
 #include <algorithm>
 #include <type_traits>
 
@@ -57,6 +59,7 @@ namespace cosa {
 namespace {
 
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
 
 // A wave-uniform read of data this kernel never writes (the count and first list entries in a
 // tile's prologue), through the constant address space: a scalar load, counted apart from the
@@ -66,43 +69,67 @@ __device__ __forceinline__ int32_t ld_uniform(const int32_t* p) {
   return *(const __attribute__((address_space(4))) int32_t*)(size_t)p;
 }
 
+// A packed sequence as the attention walks it (16 bytes: a lane reads two).
+struct PackSeq {
+  int start;       // first rank of its piece, INT_MAX past the last sequence
+  int first, len;  // first block, blocks
+  float tau;       // skip threshold
+};
+
+// The walking order of a pack (order_of): the sequences by falling length. Those before `tail` go one
+// after the other, each from its last block down; the others go together, by falling position in their
+// sequence. A piece is a range of ranks: piece k < tail is sequence k, piece k >= tail the positions that
+// exactly the sequences tail .. k have.
+struct PackOrder {
+  int n, tail;  // n == 0: not packed
+  alignas(16) PackSeq seq[kMaxPackedSeqs];
+};
+
 struct AttnParams {
   AttnArgs a;
   int Hq, Hkv, L, nb, G, n_units;
-  int group_heads;       // (batch, KV head) pairs whose query blocks are walked together (unit_tile)
+  int group_heads;  // (batch, KV head) pairs whose query blocks are walked together (unit_tile)
   float scale, scale_log2;
-  PackOrder pack_order;  // packed sequences only
+  PackOrder pack;
 };
 
-// The query block i of (batch, KV head) ng that unit u stands for, with the first block F and the
-// index of the packed sequence that holds it. The heads go in groups of P.group_heads; in a group the
-// heaviest query blocks of every head come first, so that its last tiles are the lightest ones and
-// the CUs finish together. With whole heads one after the other, the last head's heaviest blocks
-// started when the others were done (dense, 32 / 8 heads, 4K tokens 190 -> 131 us, 8K 577 -> 478 us).
-// A block's weight is its position in its sequence; packed sequences are ranked over all of them.
-__device__ __forceinline__ void unit_tile(const AttnParams& P, int u, int& ng, int& i, int& F,
-                                          int& seq) {
+// The query block i of (batch, KV head) ng that unit u stands for, with the first block F and the skip
+// threshold tau of the packed sequence that holds it (0 and the call's threshold without packing). The
+// heads go in groups of P.group_heads; in a group the heaviest query blocks of every head come first, so
+// that its last tiles are the lightest ones and the CUs finish together. With whole heads one after the
+// other, the last head's heaviest blocks started when the others were done (dense, 32 / 8 heads, 4K
+// tokens 190 -> 131 us, 8K 577 -> 478 us).
+// Packs: lane l holds the sequences 2 l (pa) and 2 l + 1 (pb) of P.pack.seq, and a count of the pieces that
+// start at or before the rank finds its own. The queries' loads wait for the block, so no memory is read
+// on the way: a search through the kernel arguments took 0.4 us of every tile (16 / 8 heads, 60 sequences
+// of 10 blocks of 128: 390 -> 385 us).
+__device__ __forceinline__ void unit_tile(const AttnParams& P, i32x4_t pa, i32x4_t pb, int u, int& ng,
+                                          int& i, int& F, float& tau) {
   const int gsz = P.group_heads * P.nb;
   const int grp = u / gsz, r = u - grp * gsz;
   const int first = grp * P.group_heads;
   const int heads = min(P.group_heads, P.n_units / P.nb - first);
   const int rank = r / heads;
   ng = first + (r - rank * heads);
-  F = 0;
-  seq = 0;
   i = P.nb - 1 - rank;
-  if (P.a.pack.n > 0) {
-    int lo = 0, hi = P.a.pack.n - 1;  // the last piece that starts at or before the rank
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (P.pack_order.start[mid] <= rank) lo = mid;
-      else hi = mid - 1;
+  F = 0;
+  tau = P.a.tau;
+  if (P.pack.n > 0) {
+    const int k = __popcll(__ballot(pa.x <= rank)) + __popcll(__ballot(pb.x <= rank)) - 1;
+    auto of = [](int even, int odd, int q) {  // the value of sequence q
+      const int e = __builtin_amdgcn_readlane(even, q >> 1), o = __builtin_amdgcn_readlane(odd, q >> 1);
+      return (q & 1) ? o : e;
+    };
+    const int len = of(pa.z, pb.z, k);  // in the tail: of the shortest sequence that reaches the piece
+    int down = rank - of(pa.x, pb.x, k), q = k;
+    if (k > P.pack.tail) {
+      const int together = k - P.pack.tail + 1, off = down;
+      down = off / together;
+      q = P.pack.tail + off - down * together;
     }
-    const int off = rank - P.pack_order.start[lo], down = off / (lo + 1);
-    const int shortest = P.pack_order.by_len[lo];  // of the lo + 1 sequences that reach the piece
-    seq = P.pack_order.by_len[off - down * (lo + 1)];
-    F = P.a.pack.cu[seq];
-    i = F + (P.a.pack.cu[shortest + 1] - P.a.pack.cu[shortest]) - down - 1;
+    F = of(pa.y, pb.y, q);
+    tau = __builtin_bit_cast(float, of(pa.w, pb.w, q));
+    i = F + len - down - 1;
   }
 }
 
@@ -256,6 +283,13 @@ void attention_kernel(const AttnParams P) {
     }
     return -1;
   };
+  // The pack's sequences, two a lane (unit_tile); read once, not behind each tile's stores.
+  i32x4_t pack_even = {0, 0, 0, 0}, pack_odd = {0, 0, 0, 0};
+  if (P.pack.n > 0) {
+    const i32x4_t* seq = reinterpret_cast<const i32x4_t*>(P.pack.seq) + 2 * (threadIdx.x & 63);
+    pack_even = seq[0];
+    pack_odd = seq[1];
+  }
   for (;;) {
   int unit, pair;
   if constexpr (PERSIST) {
@@ -283,9 +317,10 @@ void attention_kernel(const AttnParams P) {
     if (!map_tile(blockIdx.x, P.G / HPW, P.n_units, unit, pair)) return;
   }
   // Packed sequences: block i only sees the blocks F .. i of its own sequence, whose skip threshold
-  // is its own (F = 0 and the call's threshold without packing; the masked walk is never packed).
-  int ng, i, F, seq;  // ng = n * Hkv + g
-  unit_tile(P, unit, ng, i, F, seq);
+  // is its own (the masked walk is never packed).
+  int ng, i, F;  // ng = n * Hkv + g
+  float tau;
+  unit_tile(P, pack_even, pack_odd, unit, ng, i, F, tau);
   const int g = ng % P.Hkv, n = ng / P.Hkv;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, scalar
@@ -310,7 +345,6 @@ void attention_kernel(const AttnParams P) {
     for (int c = 0; c < 8; ++c) qf[c] = as_bf16x8(ldg16(qp + 16 * c));
   }
 
-  const float tau = P.a.pack.n > 0 ? P.a.pack.tau[seq] : P.a.tau;
   int cnt;
   const int32_t* lst = nullptr;
   const uint8_t* mrow = nullptr;
@@ -760,25 +794,41 @@ int heads_per_group(const Shape& sh, int heads_per_wg, int resident) {
   return (int)(g < heads ? g : heads);
 }
 
-PackOrder order_of(const SeqPack& sp) {
+// The walking order of a pack, tiles_per_block tiles to a block of it. One sequence after the other keeps
+// a sequence's pages in the L2 while its blocks are walked; only the end of the grid gains from heavy blocks
+// first, so just the shortest sequences are ranked together, as many as hold two tiles per resident
+// workgroup. All ranked together / this: 32 / 8 heads, 40 sequences of 10 blocks of 128 474 / 442 us, 100 of
+// 5 522 / 487; all one after the other / this: 4 / 1 heads, 250, 100 and 17 blocks 391 / 364, 8 / 2 heads, 40,
+// 39, 41 and five of 1 or 2 blocks 83 / 75.
+PackOrder order_of(const SeqPack& sp, long long tiles_per_block, int resident) {
   PackOrder po;
+  po.n = po.tail = sp.n;
+  if (sp.n == 0) return po;
   auto len = [&](int q) { return sp.cu[q + 1] - sp.cu[q]; };
-  for (int q = 0; q < sp.n; ++q) po.by_len[q] = q;
-  std::stable_sort(po.by_len, po.by_len + sp.n, [&](int x, int y) { return len(x) > len(y); });
-  for (int k = 0, at = 0; k < sp.n; ++k) {
-    po.start[k] = at;
-    const int next = k + 1 < sp.n ? len(po.by_len[k + 1]) : 0;
-    at += (k + 1) * (len(po.by_len[k]) - next);
+  int by_len[kMaxPackedSeqs];
+  for (int q = 0; q < sp.n; ++q) by_len[q] = q;
+  std::sort(by_len, by_len + sp.n,
+            [&](int x, int y) { return len(x) != len(y) ? len(x) > len(y) : x < y; });
+  for (long long tiles = 0; po.tail > 0 && tiles < 2LL * resident;)
+    tiles += len(by_len[--po.tail]) * tiles_per_block;
+  for (int k = 0, at = 0; k < kMaxPackedSeqs; ++k) {
+    po.seq[k] = PackSeq{INT_MAX, 0, 0, 0.f};
+    if (k >= sp.n) continue;
+    const int q = by_len[k];
+    po.seq[k] = PackSeq{at, sp.cu[q], len(q), sp.tau[q]};
+    const int next = k >= po.tail && k + 1 < sp.n ? len(by_len[k + 1]) : 0;
+    at += (k < po.tail ? 1 : k - po.tail + 1) * (len(q) - next);
   }
   return po;
 }
 
 template <int BLOCK, int HPW, int WALK, int PG>
-void launch_t(const Shape& sh, AttnParams& P, int cus, hipStream_t stream) {
+void launch_t(const Shape& sh, AttnParams& P, const SeqPack& pack, int cus, hipStream_t stream) {
   using Cfg = TileCfg<BLOCK, HPW>;
   const int slots = (P.n_units + kNumXcd - 1) / kNumXcd * kNumXcd * (sh.G / HPW);
   const int resident = cus * Cfg::kWgPerCu;
   P.group_heads = heads_per_group(sh, HPW, resident);
+  P.pack = order_of(pack, (long long)P.group_heads * (sh.G / HPW), resident);
   if constexpr (WALK == kWalkList) {
     // A queue is of no use to a grid that is resident as a whole.
     if (P.a.queue != nullptr && slots > resident) {
@@ -804,25 +854,24 @@ void launch_t(const Shape& sh, AttnParams& P, int cus, hipStream_t stream) {
 // 64-token blocks: list walks of up to one pair per CU only (dense, 4 / 1 heads, 64 blocks 72 / 75;
 // their pages are short, and fetching them once for both heads counts more).
 template <int WALK, int PG>
-void launch_shape(const Shape& sh, AttnParams& P, hipStream_t stream) {
+void launch_shape(const Shape& sh, AttnParams& P, const SeqPack& pack, hipStream_t stream) {
   const int cus = cu_count();
   const long long pairs = (long long)P.n_units * (sh.G / 2);
   const bool few = sh.b == 128 ? 2 * pairs <= 3 * cus : WALK == kWalkList && pairs <= cus;
   const bool pair = (sh.G % 2) == 0 && !few;
   if (sh.b == 128) {
-    if (pair) launch_t<128, 2, WALK, PG>(sh, P, cus, stream);
-    else launch_t<128, 1, WALK, PG>(sh, P, cus, stream);
+    if (pair) launch_t<128, 2, WALK, PG>(sh, P, pack, cus, stream);
+    else launch_t<128, 1, WALK, PG>(sh, P, pack, cus, stream);
   } else {
-    if (pair) launch_t<64, 2, WALK, PG>(sh, P, cus, stream);
-    else launch_t<64, 1, WALK, PG>(sh, P, cus, stream);
+    if (pair) launch_t<64, 2, WALK, PG>(sh, P, pack, cus, stream);
+    else launch_t<64, 1, WALK, PG>(sh, P, pack, cus, stream);
   }
 }
 
 template <int WALK>
-hipError_t launch(const Shape& sh, const AttnArgs& a, hipStream_t stream) {
+hipError_t launch(const Shape& sh, const AttnArgs& a, const SeqPack& pack, hipStream_t stream) {
   AttnParams P;
   P.a = a;
-  if (a.pack.n > 0) P.pack_order = order_of(a.pack);
   P.Hq = sh.Hq;
   P.Hkv = sh.Hkv;
   P.L = sh.L;
@@ -832,27 +881,29 @@ hipError_t launch(const Shape& sh, const AttnArgs& a, hipStream_t stream) {
   P.scale = sh.scale;
   P.scale_log2 = sh.scale * 1.4426950408889634f;
   if constexpr (WALK == kWalkList) {
-    if (a.pg.table == nullptr) launch_shape<kWalkList, kPgNone>(sh, P, stream);
-    else if ((1 << a.pg.log2_page) >= sh.b) launch_shape<kWalkList, kPgWhole>(sh, P, stream);
-    else launch_shape<kWalkList, kPgSplit>(sh, P, stream);
+    if (a.pg.table == nullptr) launch_shape<kWalkList, kPgNone>(sh, P, pack, stream);
+    else if ((1 << a.pg.log2_page) >= sh.b) launch_shape<kWalkList, kPgWhole>(sh, P, pack, stream);
+    else launch_shape<kWalkList, kPgSplit>(sh, P, pack, stream);
   } else {
-    launch_shape<WALK, kPgNone>(sh, P, stream);
+    launch_shape<WALK, kPgNone>(sh, P, pack, stream);
   }
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_osk_attention(const Shape& sh, const AttnArgs& a, hipStream_t stream) {
-  return launch<kWalkList>(sh, a, stream);
+hipError_t launch_osk_attention(const Shape& sh, const AttnArgs& a, const SeqPack& pack,
+                                 hipStream_t stream) {
+  return launch<kWalkList>(sh, a, pack, stream);
 }
 
-hipError_t launch_dense_attention(const Shape& sh, const AttnArgs& a, hipStream_t stream) {
-  return launch<kWalkDense>(sh, a, stream);
+hipError_t launch_dense_attention(const Shape& sh, const AttnArgs& a, const SeqPack& pack,
+                                 hipStream_t stream) {
+  return launch<kWalkDense>(sh, a, pack, stream);
 }
 
 hipError_t launch_masked_attention(const Shape& sh, const AttnArgs& a, hipStream_t stream) {
-  return launch<kWalkMask>(sh, a, stream);
+  return launch<kWalkMask>(sh, a, SeqPack{}, stream);
 }
 
 }  // namespace cosa

@@ -289,8 +289,8 @@ cosa_status prefill(const cosa_problem* problem, const void* q, const void* k, c
   if (e != hipSuccess) return hip_fail(e, "kap_select launch");
   cosa::AttnArgs a{static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                    static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), order, count,
-                   nullptr, nullptr, nullptr, on, tau, pg, nullptr, sp, queue, true};
-  e = cosa::launch_osk_attention(sh, a, s);
+                   nullptr, nullptr, nullptr, on, tau, pg, nullptr, queue, true};
+  e = cosa::launch_osk_attention(sh, a, sp, s);
   return e == hipSuccess ? ok() : hip_fail(e, "osk_attention launch");
 }
 
@@ -409,7 +409,7 @@ cosa_status cosa_osk_attention(const cosa_problem* problem, const void* q, const
   cosa::AttnArgs a{static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                    static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), order, count,
                    visit_log, margin_log, n_computed, on, tau, cosa::KvPages{}};
-  const hipError_t e = cosa::launch_osk_attention(sh, a, as_stream(stream));
+  const hipError_t e = cosa::launch_osk_attention(sh, a, cosa::SeqPack{}, as_stream(stream));
   return e == hipSuccess ? ok() : hip_fail(e, "osk_attention launch");
 }
 
@@ -438,8 +438,8 @@ cosa_status cosa_osk_attention_queued(const cosa_problem* problem, const void* q
   cosa::AttnArgs a{static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                    static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), order, count,
                    visit_log, margin_log, n_computed, on, tau, cosa::KvPages{}, nullptr,
-                   cosa::SeqPack{}, static_cast<uint32_t*>(queue)};
-  const hipError_t e = cosa::launch_osk_attention(sh, a, as_stream(stream));
+                   static_cast<uint32_t*>(queue)};
+  const hipError_t e = cosa::launch_osk_attention(sh, a, cosa::SeqPack{}, as_stream(stream));
   return e == hipSuccess ? ok() : hip_fail(e, "osk_attention launch");
 }
 
@@ -463,7 +463,7 @@ cosa_status cosa_osk_attention_paged(const cosa_problem* problem, const void* q,
   cosa::AttnArgs a{static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(kv->k_cache),
                    static_cast<const uint16_t*>(kv->v_cache), static_cast<uint16_t*>(o), order,
                    count, visit_log, margin_log, n_computed, on, tau, pg};
-  const hipError_t e = cosa::launch_osk_attention(sh, a, as_stream(stream));
+  const hipError_t e = cosa::launch_osk_attention(sh, a, cosa::SeqPack{}, as_stream(stream));
   return e == hipSuccess ? ok() : hip_fail(e, "osk_attention launch");
 }
 
@@ -478,7 +478,7 @@ cosa_status cosa_dense_attention(const cosa_problem* problem, const void* q, con
   cosa::AttnArgs a{static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                    static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), nullptr, nullptr,
                    nullptr, nullptr, nullptr, 0, 0.f, cosa::KvPages{}};
-  const hipError_t e = cosa::launch_dense_attention(sh, a, as_stream(stream));
+  const hipError_t e = cosa::launch_dense_attention(sh, a, cosa::SeqPack{}, as_stream(stream));
   return e == hipSuccess ? ok() : hip_fail(e, "dense_attention launch");
 }
 
@@ -629,8 +629,8 @@ cosa_status cosa_osk_attention_varlen(const cosa_problem* problem, const cosa_va
     return fail(COSA_ERR_INVALID_ARG, "q, k, v, order, count and o must be non-NULL");
   cosa::AttnArgs a{static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                    static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), order, count,
-                   visit_log, margin_log, n_computed, on, tau, cosa::KvPages{}, nullptr, sp};
-  const hipError_t e = cosa::launch_osk_attention(sh, a, as_stream(stream));
+                   visit_log, margin_log, n_computed, on, tau, cosa::KvPages{}};
+  const hipError_t e = cosa::launch_osk_attention(sh, a, sp, as_stream(stream));
   return e == hipSuccess ? ok() : hip_fail(e, "osk_attention launch");
 }
 
@@ -647,8 +647,8 @@ cosa_status cosa_dense_attention_varlen(const cosa_problem* problem, const cosa_
   if (!q || !k || !v || !o) return fail(COSA_ERR_INVALID_ARG, "q, k, v and o must be non-NULL");
   cosa::AttnArgs a{static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                    static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), nullptr, nullptr,
-                   nullptr, nullptr, nullptr, 0, 0.f, cosa::KvPages{}, nullptr, sp};
-  const hipError_t e = cosa::launch_dense_attention(sh, a, as_stream(stream));
+                   nullptr, nullptr, nullptr, 0, 0.f, cosa::KvPages{}};
+  const hipError_t e = cosa::launch_dense_attention(sh, a, sp, as_stream(stream));
   return e == hipSuccess ? ok() : hip_fail(e, "dense_attention launch");
 }
 

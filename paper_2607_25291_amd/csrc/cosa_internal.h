@@ -39,14 +39,6 @@ struct SeqPack {
   float tau[kMaxPackedSeqs];
 };
 
-// The blocks of all packed sequences by falling position in their sequence: by_len lists the sequences
-// by falling length, and the ranks start[k] .. start[k + 1] - 1 run over the positions that exactly
-// the k + 1 longest sequences have, position by position. Only read when pack.n > 0.
-struct PackOrder {
-  int by_len[kMaxPackedSeqs];
-  int start[kMaxPackedSeqs];
-};
-
 // The fraction cut as one wavefront per row takes it (select_wave.h).
 struct RowSelect {
   const float* score;
@@ -96,7 +88,6 @@ struct AttnArgs {
   float tau;              // skip threshold in nats (float32)
   KvPages pg;             // k and v are the paged caches when pg.table != nullptr (OSK only)
   const uint8_t* mask;    // block mask [B, Hkv, nb, nb] (masked walk only)
-  SeqPack pack;           // packed sequences (OSK and dense walks); tau per sequence
   uint32_t* queue;        // OSK: kOskQueueBytes of work-queue counters (persistent grid), or nullptr
   bool queue_ready;       // the counters are zero already (an earlier kernel of the stream cleared them)
 };
@@ -119,8 +110,10 @@ size_t kap_select_lds_bytes(const Shape& sh);
 
 hipError_t launch_kap_score(const Shape& sh, const KapScoreArgs& a, hipStream_t stream);
 hipError_t launch_kap_select(const Shape& sh, const KapSelectArgs& a, hipStream_t stream);
-hipError_t launch_osk_attention(const Shape& sh, const AttnArgs& a, hipStream_t stream);
-hipError_t launch_dense_attention(const Shape& sh, const AttnArgs& a, hipStream_t stream);
+hipError_t launch_osk_attention(const Shape& sh, const AttnArgs& a, const SeqPack& pack,
+                                 hipStream_t stream);
+hipError_t launch_dense_attention(const Shape& sh, const AttnArgs& a, const SeqPack& pack,
+                                 hipStream_t stream);
 hipError_t launch_masked_attention(const Shape& sh, const AttnArgs& a, hipStream_t stream);
 size_t block_mass_lds_bytes(const Shape& sh);
 hipError_t launch_block_mass(const Shape& sh, const uint16_t* q, const uint16_t* k, float* mass,

@@ -200,3 +200,40 @@ def test_prefill_equals_stages(heads, block, nb, mode, lens, page, queued, stage
     queue = ws[lay.queue:lay.queue + B.cosa_osk_attention_queue_bytes()]
     assert queue_counters(queue) == [queue_left(p, queued) if queued else 0] * 8
     assert bool((ws[lay.keys:lay.queue] != 0xFF).any()) == staged
+
+
+@pytest.mark.parametrize("heads,block,lens", [
+    # as many sequences as a call takes; two lengths, so that pieces of the order are empty
+    ((8, 4), 64, (3,) * 60 + (8,) * 8 + (3,) * 60),
+    # single heads and head pairs, the longest sequences in front, beside and behind short ones
+    ((3, 1), 128, (9,) * 20 + (31, 1, 2, 30) + (8,) * 20),
+    ((8, 2), 128, (40, 1, 7) + (5,) * 30 + (3,) * 20),
+])
+def test_packs_in_front_and_tail(heads, block, lens):
+    """Packs of which the longest sequences are walked one after the other and the rest together: dense
+    attention and a prefill with its work queue equal a call per sequence, bit for bit."""
+    Hq, Hkv = heads
+    say(f"[pack order] heads={heads} block={block} sequences={len(lens)} blocks={sum(lens)}")
+    t = torch()
+    nb, spb = sum(lens), 8
+    cus = t.cuda.get_device_properties(0).multi_processor_count
+    # two tiles per resident workgroup are ranked together, at most two heads a tile
+    assert nb * Hq > (1 if Hq % 2 else 2) * 2 * {64: 2, 128: 2 if Hq % 2 else 1}[block] * cus
+    q, k, v = random_inputs(1, Hq, Hkv, nb * block, 128, seed=nb, scale=1.5)
+    cu = np.concatenate([[0], np.cumsum(lens)]).tolist()
+    p = B.Problem(1, Hq, Hkv, nb * block, 128, block, block // spb)
+    run = Run.upload(p, q, k, v)
+    sel, sk = B.select(B.SELECT_FRACTION, 0.6), B.skip(B.SKIP_ROWMAX, 0.4 * min(lens) * block)
+    o, op = t.full_like(run.q, 0x7BCD), t.full_like(run.q, 0x7BCD)
+    B.cosa_dense_attention_varlen(p, B.varlen(cu), run.q, run.k, run.v, o)
+    nbytes = B.cosa_prefill_workspace_bytes(p)
+    ws = t.zeros(nbytes, dtype=t.uint8, device="cuda")
+    B.cosa_prefill_varlen(p, B.varlen(cu), run.q, run.k, run.v, sel, sk, ws, nbytes, op)
+    lay = B.cosa_prefill_workspace_layout(p)
+    assert queue_counters(ws[lay.queue:lay.queue + B.cosa_osk_attention_queue_bytes()])[0] > 0
+    for first, n in zip(cu, lens):
+        at = slice(first * block, (first + n) * block)
+        one = Run(B.Problem(1, Hq, Hkv, n * block, 128, block, block // spb),
+                  *(x[:, :, at].contiguous() for x in (run.q, run.k, run.v)))
+        assert t.equal(o[:, :, at], one.dense()), first
+        assert t.equal(op[:, :, at], one.prefill(sel, sk)[0]), first
