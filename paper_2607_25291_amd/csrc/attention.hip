@@ -88,14 +88,16 @@ struct PackOrder {
 struct AttnParams {
   AttnArgs a;
   int Hq, Hkv, L, nb, G, n_units;
-  int group_heads;  // (batch, KV head) pairs whose query blocks are walked together (unit_tile)
+  // The (batch, KV head) pairs whose query blocks are walked together (unit_tile): n_front groups of
+  // group_heads, then one of last_heads.
+  int group_heads, n_front, last_heads;
   float scale, scale_log2;
   PackOrder pack;
 };
 
 // The query block i of (batch, KV head) ng that unit u stands for, with the first block F and the skip
 // threshold tau of the packed sequence that holds it (0 and the call's threshold without packing). The
-// heads go in groups of P.group_heads; in a group the heaviest query blocks of every head come first, so
+// heads go in groups (group_heads_of); in a group the heaviest query blocks of every head come first, so
 // that its last tiles are the lightest ones and the CUs finish together. With whole heads one after the
 // other, the last head's heaviest blocks started when the others were done (dense, 32 / 8 heads, 4K
 // tokens 190 -> 131 us, 8K 577 -> 478 us).
@@ -106,11 +108,16 @@ struct AttnParams {
 __device__ __forceinline__ void unit_tile(const AttnParams& P, i32x4_t pa, i32x4_t pb, int u, int& ng,
                                           int& i, int& F, float& tau) {
   const int gsz = P.group_heads * P.nb;
-  const int grp = u / gsz, r = u - grp * gsz;
-  const int first = grp * P.group_heads;
-  const int heads = min(P.group_heads, P.n_units / P.nb - first);
-  const int rank = r / heads;
-  ng = first + (r - rank * heads);
+  const int grp = min(u / gsz, P.n_front), r = u - grp * gsz;
+  int rank;  // two divisions by values the compiler keeps the reciprocals of
+  if (grp < P.n_front) {
+    rank = r / P.group_heads;
+    ng = r - rank * P.group_heads;
+  } else {
+    rank = r / P.last_heads;
+    ng = r - rank * P.last_heads;
+  }
+  ng += grp * P.group_heads;
   i = P.nb - 1 - rank;
   F = 0;
   tau = P.a.tau;
@@ -777,21 +784,36 @@ int cu_count() {
   return cus;
 }
 
-// Heads whose query blocks are walked together (unit_tile). Eight, one per XCD, so that each XCD's L2
+// Which heads' query blocks are walked together (unit_tile). Eight, one per XCD, so that each XCD's L2
 // serves one head's pages at a time: with more, or with whole heads one after the other over all
 // XCDs, long contexts lose that (16 / 16 heads, 64K tokens: 3.49 ms one at a time, 2.95 by eights, 3.21
-// all at once). More, in whole eights, while a group has fewer than four tiles per resident
-// workgroup, where the idle end of every group costs more (16 / 16 heads, 12,416 tokens: 166 us by
-// eights, 162 all at once; 4K tokens 52 and 48).
+// all at once). 1, 2 and 4 heads divide the XCDs in the same way; groups of 3, 5, 6 or 7 heads send every
+// XCD through all of them and measure as one head at a time does at long contexts (dense, 4 query heads
+// per KV head, 64K tokens: 3 heads 11.08 / 11.14 ms, 5 18.56 / 18.54, 6 22.2 / 21.9, 7 25.98 / 26.09) and
+// better at short ones (8K: 247 / 208, 382 / 330, 440 / 385, 504 / 441 us).
+// More where few tiles would leave CUs idle at the end (dense, 16 / 16 heads, 4K tokens 52 us by eights, 48
+// all together). List walks: only the end of the grid has an idle end, so the last group takes the heads
+// that are left once it holds two tiles per resident workgroup, and the groups in front of it stay at
+// eight. When every group grew to four tiles per workgroup, batches of short sequences lost their L2 to it
+// (prefill, 32 / 8 heads, 16 sequences of 16 blocks of 128 345 -> 335 us, 40 of 10 446 -> 440; 20 / 20 heads,
+// 97 blocks 265 -> 250). Dense and masked walks keep growing every group, in whole eights: a tile's weight
+// there is its position alone, and the heaviest first over all heads counts more (dense, 8 / 8 heads, 30
+// sequences of 12 blocks: front groups of eight 196 us, all grown 186).
 // Four where head pairs walk contexts of which eight heads' K and V exceed the 256 MiB last-level
-// cache (32 / 8 heads, 128K tokens: 9.99 ms by eights, 9.95 by fours; single heads, whose pages
-// are read once per head, gain from eights there: 8 / 8 heads 3.37 and 3.44 ms).
-int heads_per_group(const Shape& sh, int heads_per_wg, int resident) {
-  const int heads = sh.B * sh.Hkv, tiles_per_unit = sh.G / heads_per_wg;
+// cache (by eights / by fours: 32 / 8 heads, prefill 768 blocks of 128 5.99 / 5.95 ms, 1024 10.27 / 10.22,
+// masked 8.45 / 8.21; 16 / 8 heads, 1024 blocks, prefill 5.53 / 5.46, masked 7.78 / 7.33; dense the same
+// within 0.2 %). Single heads, whose pages are read once per head, gain from eights there: 8 / 8 heads,
+// 1024 blocks 3.37 and 3.44 ms.
+void group_heads_of(AttnParams& P, const Shape& sh, int heads_per_wg, bool list, int resident) {
+  const int heads = sh.B * sh.Hkv;
+  const long long tiles = (long long)sh.nb * (sh.G / heads_per_wg);  // of one head
   const bool over_cache = 8LL * sh.L * kHeadDim * 4 > (256LL << 20);
   long long g = heads_per_wg == 2 && over_cache ? 4 : 8;
-  while (g < heads && g * sh.nb * tiles_per_unit < 4LL * resident) g += 8;
-  return (int)(g < heads ? g : heads);
+  while (!list && g < heads && g * tiles < 4LL * resident) g += 8;
+  const long long last = list ? std::max(1LL, (2LL * resident + tiles - 1) / tiles) : 1;
+  P.group_heads = (int)std::min<long long>(g, heads);
+  P.n_front = heads > last ? (int)((heads - last) / P.group_heads) : 0;
+  P.last_heads = heads - P.n_front * P.group_heads;
 }
 
 // The walking order of a pack, tiles_per_block tiles to a block of it. One sequence after the other keeps
@@ -827,8 +849,8 @@ void launch_t(const Shape& sh, AttnParams& P, const SeqPack& pack, int cus, hipS
   using Cfg = TileCfg<BLOCK, HPW>;
   const int slots = (P.n_units + kNumXcd - 1) / kNumXcd * kNumXcd * (sh.G / HPW);
   const int resident = cus * Cfg::kWgPerCu;
-  P.group_heads = heads_per_group(sh, HPW, resident);
-  P.pack = order_of(pack, (long long)P.group_heads * (sh.G / HPW), resident);
+  group_heads_of(P, sh, HPW, WALK == kWalkList, resident);
+  P.pack = order_of(pack, (long long)P.last_heads * (sh.G / HPW), resident);
   if constexpr (WALK == kWalkList) {
     // A queue is of no use to a grid that is resident as a whole.
     if (P.a.queue != nullptr && slots > resident) {

@@ -237,3 +237,33 @@ def test_packs_in_front_and_tail(heads, block, lens):
                   *(x[:, :, at].contiguous() for x in (run.q, run.k, run.v)))
         assert t.equal(o[:, :, at], one.dense()), first
         assert t.equal(op[:, :, at], one.prefill(sel, sk)[0]), first
+
+
+@pytest.mark.parametrize("batch,heads,block,nb", [
+    # one group of eight heads in front of the last one, and several; single heads and head pairs, a last
+    # group of five
+    (5, (8, 8), 128, 66), (3, (16, 8), 64, 140), (9, (8, 4), 128, 64), (2, (13, 13), 64, 300),
+])
+def test_head_groups(batch, heads, block, nb):
+    """Batches whose (batch, KV head) pairs are walked in several groups: dense attention and a prefill
+    with its work queue equal a call per batch entry, bit for bit."""
+    Hq, Hkv = heads
+    say(f"[head groups] batch={batch} heads={heads} block={block} nb={nb}")
+    t = torch()
+    L = nb * block
+    per_cu = {(128, 2): 1, (128, 1): 2, (64, 2): 2, (64, 1): 4}[block, 1 if Hq == Hkv else 2]
+    cus = t.cuda.get_device_properties(0).multi_processor_count
+    tiles = nb * (1 if Hq == Hkv else Hq // Hkv // 2)
+    assert batch * Hkv - 8 >= 2 * cus * per_cu / tiles  # list walks: what the last group holds
+    q, k, v = random_inputs(1, Hq, Hkv, L, 128, seed=nb, scale=1.5)
+    one = Run.upload(B.Problem(1, Hq, Hkv, L, 128, block, block // 4), q, k, v)
+    # the entries of the batch: the heads' rows rotated by whole blocks
+    turned = [[x.roll(n * 3 * block, 2) for x in (one.q, one.k, one.v)] for n in range(batch)]
+    run = Run(B.Problem(batch, Hq, Hkv, L, 128, block, block // 4),
+              *(t.cat(x).contiguous() for x in zip(*turned)))
+    sel, sk = B.select(B.SELECT_FRACTION, 0.1), B.skip(B.SKIP_ROWMAX, 0.4 * L)
+    o, op = run.dense(), run.prefill(sel, sk)[0]
+    for n, x in enumerate(turned):
+        alone = Run(one.problem, *(y.contiguous() for y in x))
+        assert t.equal(o[n], alone.dense()[0]), n
+        assert t.equal(op[n], alone.prefill(sel, sk)[0][0]), n
