@@ -12,8 +12,8 @@
 // spent on staging), double-buffered. Each wave works through its pages in two halves,
 //   QK(m): Q K^T of page m, the diagonal mask, the new running max and the wave's skip vote;
 //   PV(m): the skip decision from the votes, softmax, P V of page m;
-// with a workgroup barrier after each half. With two heads of 128-row tiles the waves of the second
-// head start one barrier later, so phase 2m runs QK(m) of head 0 beside PV(m-1) of head 1 and phase
+// with a workgroup barrier after each half. With two heads of 128-row tiles the waves of the second head start one barrier later, so phase 2m runs
+// QK(m) of head 0 beside PV(m-1) of head 1 and phase
 // 2m+1 runs PV(m) of head 0 beside QK(m) of head 1. Waves w and w + 4 share a SIMD: while one
 // issues the Q K^T MFMAs the other runs its softmax VALU work and P V MFMAs. The waves of head 0
 // fetch K pages (page m+1 at the end of QK(m), after its vote), those of head 1 V pages (page m+1
@@ -23,8 +23,8 @@
 // of delaying the Q K^T chain. A wave waits for its own copies at the end of its PV half, so every
 // copy has the rest of its phase and the next one to land before the barrier that publishes it.
 //
-// With one head in a workgroup (an odd number of query heads per KV head, or few tiles) nothing inside the workgroup
-// fills the other's waits, so it keeps one page buffer per tensor instead of two and several
+// With one head in a workgroup (an odd number of query heads per KV head, or few tiles) nothing inside
+// the workgroup fills the other's waits, so it keeps one page buffer per tensor instead of two and several
 // workgroups share a CU (two of b = 128, four of b = 64: two waves per SIMD again), each at its own
 // point of the walk. The next K page is fetched during PV(m) and the next V page during QK(m+1).
 // Against double-buffered pages at one wave per SIMD: dense 28 / 4 heads, 9,856 tokens 867 -> 630 us;
@@ -91,6 +91,7 @@ struct AttnParams {
   // The (batch, KV head) pairs whose query blocks are walked together (unit_tile): n_front groups of
   // group_heads, then one of last_heads.
   int group_heads, n_front, last_heads;
+  int fold;  // resident grids of more than one workgroup a CU: CUs of an XCD, otherwise 0
   float scale, scale_log2;
   PackOrder pack;
 };
@@ -247,7 +248,7 @@ __global__ void queue_reset(uint32_t* queue) {
   if (threadIdx.x < kNumXcd) queue[threadIdx.x * kOskQueueStep] = 0u;
 }
 
-template <int BLOCK, int HPW, int WALK, int PG, bool PERSIST>
+template <int BLOCK, int HPW, int WALK, int PG, bool PERSIST, bool STAGGER>
 __global__ __attribute__((amdgpu_flat_work_group_size(TileCfg<BLOCK, HPW>::kThreads,
                                                       TileCfg<BLOCK, HPW>::kThreads)))
 __attribute__((amdgpu_waves_per_eu(TileCfg<BLOCK, HPW>::kWavesPerEu,
@@ -321,7 +322,13 @@ void attention_kernel(const AttnParams P) {
     if (ps < 0) return;
     if (!map_tile(ps, P.G / HPW, P.n_units, unit, pair)) continue;
   } else {
-    if (!map_tile(blockIdx.x, P.G / HPW, P.n_units, unit, pair)) return;
+    int p = blockIdx.x;
+    if (P.fold > 0) {  // rounds of P.fold workgroups an XCD, every second one backwards (launch_t)
+      const int k = p >> 3, round = k / P.fold, first = round * P.fold;
+      const int last = min(first + P.fold, (int)gridDim.x >> 3) - 1;
+      if (round & 1) p = ((first + last - k) << 3) | (p & 7);
+    }
+    if (!map_tile(p, P.G / HPW, P.n_units, unit, pair)) return;
   }
   // Packed sequences: block i only sees the blocks F .. i of its own sequence, whose skip threshold
   // is its own (the masked walk is never packed).
@@ -734,11 +741,7 @@ void attention_kernel(const AttnParams P) {
     tbl_nxt = tbl_nxt2;
   };
 
-  // With b = 128 the two heads' waves share SIMDs and head slot 1 runs one phase behind. With b = 64
-  // they sit on different SIMDs, and it is another workgroup's wave that fills a SIMD's gaps: there
-  // both heads run the same phase, so that a Q K^T half does not wait for the partner's P V (packed
-  // 25K tokens, 16 / 4 heads 209.5 -> 203.6 us; 32 / 8 heads, 16K tokens 544 -> 520 us).
-  constexpr bool STAGGER = HPW == 2 && BLOCK == 128;
+  // Head slot 1 runs one phase behind (launch_t says where).
   if (STAGGER && hw == 1) end_phase(false);
   if constexpr (Cfg::kStages == 1) {
     for (int kk = 0; kk < cnt; ++kk) page(kk, std::integral_constant<int, 0>{});
@@ -851,6 +854,17 @@ void launch_t(const Shape& sh, AttnParams& P, const SeqPack& pack, int cus, hipS
   const int resident = cus * Cfg::kWgPerCu;
   group_heads_of(P, sh, HPW, WALK == kWalkList, resident);
   P.pack = order_of(pack, (long long)P.last_heads * (sh.G / HPW), resident);
+  // A grid that is resident as a whole, two or more workgroups to a CU: the CUs get their first
+  // workgroups heaviest first, and their second ones lightest first, so that no CU holds the heavy tiles
+  // of both rounds. All rounds heaviest first / folded, us: b = 64, 4 / 1 heads, 250 blocks, every block
+  // kept 398 / 376, dense 331 / 309; b = 128, dense, 32 / 8 heads, 16 blocks 48.6 / 46.2, 8 / 2 heads, 64
+  // blocks 167.5 / 156.8, prefill 91.8 / 87.2.
+  P.fold = slots <= resident && slots > cus ? cus / kNumXcd : 0;
+  // Head pairs. With b = 128 the two heads' waves share SIMDs, and the second head runs one phase behind
+  // the first. With b = 64 they sit on different SIMDs, and it is another workgroup's wave that fills a
+  // SIMD's gaps: there both heads run the same phase, so that a Q K^T half does not wait for the partner's
+  // P V (packed 25K tokens, 16 / 4 heads 209.5 -> 203.6 us; 32 / 8 heads, 16K tokens 544 -> 520 us).
+  constexpr bool kBehind = HPW == 2 && BLOCK == 128;
   if constexpr (WALK == kWalkList) {
     // A queue is of no use to a grid that is resident as a whole.
     if (P.a.queue != nullptr && slots > resident) {
@@ -859,12 +873,12 @@ void launch_t(const Shape& sh, AttnParams& P, const SeqPack& pack, int cus, hipS
       // against one).
       if (!P.a.queue_ready)
         hipLaunchKernelGGL(queue_reset, dim3(1), dim3(64), 0, stream, P.a.queue);
-      hipLaunchKernelGGL((attention_kernel<BLOCK, HPW, WALK, PG, true>),
+      hipLaunchKernelGGL((attention_kernel<BLOCK, HPW, WALK, PG, true, kBehind>),
                          dim3(resident), dim3(Cfg::kThreads), 0, stream, P);
       return;
     }
   }
-  hipLaunchKernelGGL((attention_kernel<BLOCK, HPW, WALK, PG, false>), dim3(slots),
+  hipLaunchKernelGGL((attention_kernel<BLOCK, HPW, WALK, PG, false, kBehind>), dim3(slots),
                      dim3(Cfg::kThreads), 0, stream, P);
 }
 

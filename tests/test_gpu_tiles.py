@@ -267,3 +267,45 @@ def test_head_groups(batch, heads, block, nb):
         alone = Run(one.problem, *(y.contiguous() for y in x))
         assert t.equal(o[n], alone.dense()[0]), n
         assert t.equal(op[n], alone.prefill(sel, sk)[0][0]), n
+
+
+@pytest.mark.parametrize("heads,block,nb", [
+    # two workgroups a compute unit: head pairs of 64-token blocks, single heads of 128-token blocks; the last
+    # round full, nearly empty, and of one workgroup an XCD
+    ((4, 1), 64, 256), ((4, 1), 64, 150), ((8, 4), 64, 66), ((3, 1), 128, 100), ((4, 4), 128, 66),
+    # up to four: single heads of 64-token blocks
+    ((5, 1), 64, 150), ((3, 1), 64, 256), ((1, 1), 64, 256),
+    # the first grid beyond one workgroup a unit, dense grids on either side of 5/3 rounds, short walks
+    ((2, 2), 128, 129), ((8, 2), 64, 212), ((8, 2), 64, 214), ((16, 4), 64, 31),
+])
+def test_resident_grids(heads, block, nb):
+    """Grids that are resident as a whole with several workgroups to a compute unit, and those a little
+    larger: every walk equals a call per query head (at most one workgroup a unit), bit for bit."""
+    Hq, Hkv = heads
+    say(f"[resident] heads={heads} block={block} nb={nb}")
+    t = torch()
+    L, G = nb * block, Hq // Hkv
+    q, k, v = random_inputs(1, Hq, Hkv, L, 128, seed=nb, scale=1.5)
+    run = Run.upload(B.Problem(1, Hq, Hkv, L, 128, block, block // 8), q, k, v)
+    rng = np.random.default_rng(nb)
+    mask = (np.tril(rng.random((1, Hkv, nb, nb)) < 0.2) | np.eye(nb, dtype=bool)).astype(np.uint8)
+    order = np.full((1, Hkv, nb, nb), -1, np.int32)
+    for g, i in np.ndindex(Hkv, nb):
+        at = rng.permutation(np.flatnonzero(mask[0, g, i]))
+        order[0, g, i, :len(at)] = at
+    dm, do, dc = dev(mask), dev(order), dev(mask.sum(-1).astype(np.int32))
+    sk = B.skip(B.SKIP_ROWMAX, L * math.exp(-1.0))
+    dense, masked = run.dense(), t.full_like(run.q, 0x7BCD)
+    B.cosa_masked_attention(run.problem, run.q, run.k, run.v, dm, masked)
+    lists = [run.osk(do, dc, s) for s in (None, sk)]
+    for h in range(Hq):
+        g = h // G
+        one = Run(B.Problem(1, 1, 1, L, 128, block, block // 8), run.q[:, h].contiguous(),
+                  run.k[:, g].contiguous(), run.v[:, g].contiguous())
+        assert t.equal(dense[:, h], one.dense()[:, 0]), h
+        o = t.full_like(dense[:, :1], 0x7BCD)
+        B.cosa_masked_attention(one.problem, one.q, one.k, one.v, dm[:, g].contiguous(), o)
+        assert t.equal(masked[:, h], o[:, 0]), h
+        for s, got in zip((None, sk), lists):
+            ref = one.osk(do[:, g].contiguous(), dc[:, g].contiguous(), s)
+            assert all(t.equal(x[:, h], y[:, 0]) for x, y in zip(got, ref)), h
