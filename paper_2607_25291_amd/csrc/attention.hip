@@ -12,7 +12,8 @@
 // spent on staging), double-buffered. Each wave works through its pages in two halves,
 //   QK(m): Q K^T of page m, the diagonal mask, the new running max and the wave's skip vote;
 //   PV(m): the skip decision from the votes, softmax, P V of page m;
-// with a workgroup barrier after each half. With two heads of 128-row tiles the waves of the second head start one barrier later, so phase 2m runs
+// with a workgroup barrier after each half. With two heads of 128-row tiles (and in some grids of
+// 64-row tiles, launch_t) the waves of the second head start one barrier later, so phase 2m runs
 // QK(m) of head 0 beside PV(m-1) of head 1 and phase
 // 2m+1 runs PV(m) of head 0 beside QK(m) of head 1. Waves w and w + 4 share a SIMD: while one
 // issues the Q K^T MFMAs the other runs its softmax VALU work and P V MFMAs. The waves of head 0
@@ -863,8 +864,16 @@ void launch_t(const Shape& sh, AttnParams& P, const SeqPack& pack, int cus, hipS
   // Head pairs. With b = 128 the two heads' waves share SIMDs, and the second head runs one phase behind
   // the first. With b = 64 they sit on different SIMDs, and it is another workgroup's wave that fills a
   // SIMD's gaps: there both heads run the same phase, so that a Q K^T half does not wait for the partner's
-  // P V (packed 25K tokens, 16 / 4 heads 209.5 -> 203.6 us; 32 / 8 heads, 16K tokens 544 -> 520 us).
-  constexpr bool kBehind = HPW == 2 && BLOCK == 128;
+  // P V (packed 25K tokens, 16 / 4 heads 209.5 -> 203.6 us; 32 / 8 heads, 16K tokens 544 -> 520 us). Unless
+  // nothing is skipped (every phase then has a P V half) and there is seldom another workgroup on the CU:
+  // a resident grid, or a dense one of long walks that is not much larger. Same phase / one behind, us,
+  // 4 / 1 heads: 250 blocks, every block kept 376 / 353, masked 183 / 174, dense 309 / 303; dense, 400
+  // blocks (800 tiles) 661 / 644, 430 (860) 735 / 728, 440 (880) 767 / 778; 16 / 4 heads, 100 (800)
+  // 169 / 173. With blocks skipped the same phase stays ahead, 198 / 212, and in short walks, where the
+  // one phase more counts: 32 / 8 heads, 24 blocks, 30 % kept 27.9 / 28.4.
+  const bool long_dense = WALK == kWalkDense && sh.nb >= 128;
+  const bool behind =
+      !P.a.skip_on && sh.nb >= 32 && 3LL * slots <= (long_dense ? 5LL : 3LL) * resident;
   if constexpr (WALK == kWalkList) {
     // A queue is of no use to a grid that is resident as a whole.
     if (P.a.queue != nullptr && slots > resident) {
@@ -873,13 +882,17 @@ void launch_t(const Shape& sh, AttnParams& P, const SeqPack& pack, int cus, hipS
       // against one).
       if (!P.a.queue_ready)
         hipLaunchKernelGGL(queue_reset, dim3(1), dim3(64), 0, stream, P.a.queue);
-      hipLaunchKernelGGL((attention_kernel<BLOCK, HPW, WALK, PG, true, kBehind>),
+      hipLaunchKernelGGL((attention_kernel<BLOCK, HPW, WALK, PG, true, HPW == 2 && BLOCK == 128>),
                          dim3(resident), dim3(Cfg::kThreads), 0, stream, P);
       return;
     }
   }
-  hipLaunchKernelGGL((attention_kernel<BLOCK, HPW, WALK, PG, false, kBehind>), dim3(slots),
-                     dim3(Cfg::kThreads), 0, stream, P);
+  if (HPW == 2 && (BLOCK == 128 || behind))
+    hipLaunchKernelGGL((attention_kernel<BLOCK, HPW, WALK, PG, false, HPW == 2>), dim3(slots),
+                       dim3(Cfg::kThreads), 0, stream, P);
+  else if constexpr (HPW == 1 || BLOCK == 64)
+    hipLaunchKernelGGL((attention_kernel<BLOCK, HPW, WALK, PG, false, false>), dim3(slots),
+                       dim3(Cfg::kThreads), 0, stream, P);
 }
 
 // Two heads per workgroup where the group size is even, unless there are few tiles, at most three
