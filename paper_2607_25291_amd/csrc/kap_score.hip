@@ -20,6 +20,7 @@
 //     prefills the same workgroup then takes the row's selection.
 // Both place work so that each XCD serves as few KV heads as possible (their sampled keys then stay
 // in that XCD's L2), heaviest query blocks first.
+#include <algorithm>
 #include <mutex>
 
 #include "cosa_device.h"
@@ -348,7 +349,7 @@ __device__ __forceinline__ void score_column(int R, const float* mu, const float
 // (small problems, whose selection as a kernel of its own is mostly the launch).
 template <int SPB, int RT, bool PAGED, bool STAGED, bool SELECT>
 __global__ __launch_bounds__(kScoreThreads) void kap_score_kernel(const KapParams P) {
-  extern __shared__ __attribute__((aligned(16))) float beta[];  // [R][nbp]
+  extern __shared__ __attribute__((aligned(16))) float beta[];  // [R][nbp], blocks from F on
   __shared__ float mu[RT * 32], mu2[RT * 32];
   __shared__ float wmax[kScoreWaves][RT * 32];  // each wave's row maxima
 
@@ -377,7 +378,7 @@ __global__ __launch_bounds__(kScoreThreads) void kap_score_kernel(const KapParam
       f32x16_t acc = chunk_logits(kf, qf[rt]);
       const int row = rt * 32 + l32;
       causal_mask<SPB>(acc, chunk, i, row % SPB, half);
-      float* brow = beta + row * P.nbp;
+      float* brow = beta + row * P.nbp - F;
       const bool row_ok = row < P.R;
       block_maxima<SPB>(acc, chunk, half, [&](int, int j, float bm, bool owner) {
         const float bs = bm * P.scale;
@@ -409,7 +410,7 @@ __global__ __launch_bounds__(kScoreThreads) void kap_score_kernel(const KapParam
   for (int j = F + tid; j <= i; j += kScoreThreads)
     score_column(P.R, mu, mu2, [&](int row, float (&b)[4]) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) b[r] = beta[(row + r) * P.nbp + j];
+      for (int r = 0; r < 4; ++r) b[r] = beta[(row + r) * P.nbp + j - F];
     }, srow[j], hrow[j]);
   if constexpr (SELECT) {
     clear_queue(P.a.queue);
@@ -898,7 +899,7 @@ bool pair_applies(const Shape& sh) {
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 template <int SPB>
-hipError_t launch_spb(const Shape& sh, KapParams& P, size_t lds, hipStream_t stream) {
+hipError_t launch_spb(const Shape& sh, KapParams& P, hipStream_t stream) {
   if (P.a.kstage != nullptr) {
     const int waves = (P.n_units / P.nb) * P.nch_all;
     if (P.a.pg.table != nullptr)
@@ -912,8 +913,18 @@ hipError_t launch_spb(const Shape& sh, KapParams& P, size_t lds, hipStream_t str
                                         align256(stage_keys_bytes(sh)));
       return launch_pair<SPB>(P, pair_grid(sh), pair_lds_bytes(sh), stream);
     }
-    return launch_rt<SPB, false, true>(P, lds, stream);
   }
+  // A row's block maxima are those of its own sequence: the longest one sizes the LDS, so that a pack of
+  // many short sequences leaves room for several workgroups on a CU (prefill, us: 16 / 4 heads, 100
+  // sequences of 10 blocks of 128 560 -> 554, 8 / 2 heads, 90 of 10 266.6 -> 264.4, 4 / 1 heads, 40 of 30
+  // 277.5 -> 274.3). An odd row stride keeps the rows off each other's banks.
+  if (P.a.pack.n > 0) {
+    int longest = 0;
+    for (int q = 0; q < P.a.pack.n; ++q) longest = std::max(longest, P.a.pack.cu[q + 1] - P.a.pack.cu[q]);
+    P.nbp = std::min(P.nbp, (longest + 1) | 1);
+  }
+  const size_t lds = (size_t)P.R * P.nbp * sizeof(float);
+  if (P.a.kstage != nullptr) return launch_rt<SPB, false, true>(P, lds, stream);
   if (P.a.sel.order != nullptr) {
     if (P.a.pg.table != nullptr) return launch_rt<SPB, true, false, true>(P, lds, stream);
     return launch_rt<SPB, false, false, true>(P, lds, stream);
@@ -976,12 +987,11 @@ hipError_t launch_kap_score(const Shape& sh, const KapScoreArgs& a, hipStream_t 
   P.nch_all = (sh.L / sh.s + 31) / 32;
   P.n_units = sh.B * sh.Hkv * sh.nb;
   P.scale = sh.scale;
-  const size_t lds = kap_score_lds_bytes(sh);
   switch (sh.spb) {
-    case 4: return launch_spb<4>(sh, P, lds, stream);
-    case 8: return launch_spb<8>(sh, P, lds, stream);
-    case 16: return launch_spb<16>(sh, P, lds, stream);
-    default: return launch_spb<32>(sh, P, lds, stream);
+    case 4: return launch_spb<4>(sh, P, stream);
+    case 8: return launch_spb<8>(sh, P, stream);
+    case 16: return launch_spb<16>(sh, P, stream);
+    default: return launch_spb<32>(sh, P, stream);
   }
 }
 

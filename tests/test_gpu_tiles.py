@@ -139,6 +139,8 @@ def test_packed_tiles(lens, heads, block):
     ((16, 8), 64, 99, B.SELECT_FRACTION, (2, 63, 1, 33), 0, 2, True),
     ((16, 8), 64, 99, B.SELECT_FRACTION, (2, 63, 1, 33), 32, 2, True),
     ((8, 8), 128, 99, B.SELECT_TOP_P, (2, 63, 34), 128, 1, True),
+    # packed and staged, 64 rows a query block
+    ((16, 2), 64, 172, B.SELECT_FRACTION, (140, 2, 30), 0, 2, True),
     # packed and in place, from pages
     ((8, 8), 128, 75, B.SELECT_FRACTION, (3, 60, 12), 16, 1, False),
 ])
