@@ -4,10 +4,11 @@
 // One workgroup per (batch n, KV head g, query block i) takes H query heads of the group at a time:
 // b/32 waves per head, 32 query rows per wave. It walks the keys c <= the block's last row twice, in
 // stages of 64 keys that every wave reads from LDS (double-buffered direct loads, the K layout of the
-// attention kernel, S^T = K Q^T, one query row per lane): pass 1 keeps each lane's running maximum
-// and sum of exp over its keys (the two lanes of a row are merged after the walk), pass 2 adds each
-// block's probability sum, exp(s - m) / l over the wave's rows and the block's causal keys. The
-// waves' sums of a block meet in LDS and are added in a fixed order, so the result is deterministic.
+// attention kernel, S^T = K Q^T, one query row per lane pair): pass 1 keeps each row's running maximum
+// (over its two lanes, tile by tile) and each lane's sum of exp over its keys (the two are added after
+// the walk), pass 2 adds each block's probability sum, exp(s - m) / l over the wave's rows and the
+// block's causal keys. The waves' sums of a block meet in LDS and are added in a fixed order, so the
+// result is deterministic.
 //
 // Bound: vector ALU. A 32x32 tile of logits costs 256 MFMA cycles per SIMD and a little more of
 // maximum, fma, exp2 and add, so four waves per SIMD (128 VGPRs) run one tile's MFMAs beside the
@@ -172,9 +173,10 @@ void block_mass_kernel(const MassParams P) {
 #pragma unroll
     for (int c = 0; c < 8; ++c) qf[c] = as_bf16x8(ldg16(qp + 16 * c));
 
-    // Pass 1: this lane's maximum mb (logit * scale * log2 e) and sum of 2^(x - mb). A lane that has
-    // seen masked keys (-inf) only keeps the lowest finite value and a sum of 0. The sum moves to a
-    // new maximum by 2^(mb - mbn) of the rounded maxima, which is what its terms were formed with.
+    // Pass 1: the row's maximum mb (logit * scale * log2 e), the same in its two lanes, and this lane's
+    // sum of 2^(x - mb). Until the first finite logit mb is the lowest finite value, against which a masked
+    // key (-inf) adds 0. The sum moves to a new maximum by 2^(mb - mbn) of the rounded maxima, which is
+    // what its terms were formed with.
     // What each addition rounds off is carried along (Kahan): a row that one key dominates would
     // otherwise lose every tile of tiny terms, and its masses come out large by as much.
     float mb = -__FLT_MAX__, l = 0.f, lost = 0.f;
@@ -193,7 +195,9 @@ void block_mass_kernel(const MassParams P) {
       lost = (l - base) - y;
       mb = mbn;
     }, [](int) {});
-    // The row's two lanes together.
+    // mrow is mb and the factor 1: both lanes hold the row's maximum. Written as plainly as that, pass 1's
+    // loop is scheduled differently and the kernel takes 2 % longer (32 / 8 heads, 8K tokens 561 / 565 us,
+    // 7 / 1 heads, 60 blocks of 128 1285 / 1314).
     const float mrow = half_max(mb);
     const float inv = 1.f / half_sum((l - lost) * __builtin_amdgcn_exp2f(mb - mrow));
 

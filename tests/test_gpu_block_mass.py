@@ -69,7 +69,7 @@ def test_block_mass_sampled_32k():
     ((10, 2), 128, 3, 1), ((2, 1), 128, 7, 1), ((8, 1), 64, 6, 1), ((12, 3), 128, 4, 1)])
 def test_block_mass_head_groups(heads, block, nb, batch):
     """One, two and four query heads per workgroup, one and several passes over the group, both block
-    sizes and the first rows of the first block (whose lanes see masked keys only)."""
+    sizes and the first rows of the first block (which see whole tiles of masked keys)."""
     Hq, Hkv = heads
     say(f"[block mass] heads={heads} block={block} nb={nb} batch={batch}")
     w = Workload("m", batch, Hq, Hkv, nb * block, 128, block, block // 8, 0.5, 0.25, 64, 0.02)
