@@ -54,6 +54,8 @@ __device__ __forceinline__ float mask_above(float v, int d) {
 
 constexpr int kStageKeys = 64;
 constexpr int kStageBytes = kStageKeys * kHeadDim * 2;
+// The key stages, the waves' sums and a mass for every block fit the LDS of a CU.
+static_assert(2 * kStageBytes + 2 * 16 * 4 + kMaxBlocks * 4 <= 160 * 1024, "LDS of block_mass_kernel");
 
 template <int BLOCK, int H>
 __global__ __attribute__((amdgpu_flat_work_group_size(BLOCK * 2 * H, BLOCK * 2 * H)))
@@ -267,13 +269,11 @@ hipError_t launch_heads(const MassParams& P, size_t lds, hipStream_t stream) {
 
 }  // namespace
 
-size_t block_mass_lds_bytes(const Shape& sh) { return (size_t)sh.nb * sizeof(float); }
-
 hipError_t launch_block_mass(const Shape& sh, const uint16_t* q, const uint16_t* k, float* mass,
                              hipStream_t stream) {
   MassParams P{q, k, mass, sh.Hq, sh.Hkv, sh.L, sh.nb, sh.G, sh.B * sh.Hkv * sh.nb,
                sh.scale * 1.4426950408889634f};
-  const size_t lds = block_mass_lds_bytes(sh);
+  const size_t lds = (size_t)sh.nb * sizeof(float);
   return sh.b == 128 ? launch_heads<128>(P, lds, stream) : launch_heads<64>(P, lds, stream);
 }
 

@@ -76,7 +76,8 @@ cosa_status make_shape(const cosa_problem* p, cosa::Shape& sh, bool& empty) {
   sh.G = p->n_q_heads / p->n_kv_heads;
   sh.spb = p->block / p->stride;
   sh.scale = p->sm_scale > 0.f ? p->sm_scale : (float)(1.0 / sqrt((double)p->head_dim));
-  if (sh.nb > 8192) return fail(COSA_ERR_UNSUPPORTED, "%d blocks (supported: <= 8192)", sh.nb);
+  if (sh.nb > cosa::kMaxBlocks)
+    return fail(COSA_ERR_UNSUPPORTED, "%d blocks (supported: <= %d)", sh.nb, cosa::kMaxBlocks);
   // grid sizes and 32-bit index arithmetic inside the kernels
   const long long units = (long long)sh.B * sh.Hkv * sh.nb;
   if (units * sh.G + 8LL * sh.G > (1LL << 30) || (long long)sh.L * cosa::kHeadDim >= (1LL << 31))
@@ -506,8 +507,6 @@ cosa_status cosa_block_mass(const cosa_problem* problem, const void* q, const vo
   if (st != COSA_OK) return st;
   if (empty) return ok();
   if (!q || !k || !mass) return fail(COSA_ERR_INVALID_ARG, "q, k and mass must be non-NULL");
-  if (cosa::block_mass_lds_bytes(sh) > 160 * 1024)
-    return fail(COSA_ERR_UNSUPPORTED, "%d blocks exceed the block-mass kernel's LDS", sh.nb);
   const hipError_t e = cosa::launch_block_mass(sh, static_cast<const uint16_t*>(q),
                                                static_cast<const uint16_t*>(k), mass,
                                                as_stream(stream));

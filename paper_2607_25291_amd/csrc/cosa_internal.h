@@ -9,6 +9,7 @@
 namespace cosa {
 
 constexpr int kHeadDim = 128;
+constexpr int kMaxBlocks = 8192;  // blocks of a sequence
 constexpr int kNumXcd = 8;  // MI355X: 8 accelerator complex dies, workgroups dispatched round-robin
 
 // Shape of one validated problem (all sizes in elements).
@@ -115,7 +116,6 @@ hipError_t launch_osk_attention(const Shape& sh, const AttnArgs& a, const SeqPac
 hipError_t launch_dense_attention(const Shape& sh, const AttnArgs& a, const SeqPack& pack,
                                  hipStream_t stream);
 hipError_t launch_masked_attention(const Shape& sh, const AttnArgs& a, hipStream_t stream);
-size_t block_mass_lds_bytes(const Shape& sh);
 hipError_t launch_block_mass(const Shape& sh, const uint16_t* q, const uint16_t* k, float* mass,
                              hipStream_t stream);
 

@@ -77,3 +77,25 @@ def test_block_mass_head_groups(heads, block, nb, batch):
     got = gpu_mass(w, q, k)
     ref = O.block_mass(q, k, n_kv_heads=Hkv, block=block)
     np.testing.assert_allclose(got, ref, rtol=2e-4, atol=1e-5 * Hq // Hkv * block)
+
+
+def test_block_mass_most_blocks():
+    """The most blocks a call takes (8192): every row's masses sum to the rows of its block, sampled rows
+    against float64, and one block more is refused."""
+    t = torch()
+    nb, b, D = 8192, 64, 128
+    say(f"[block mass] most blocks: nb={nb} block={b}")
+    gen = t.Generator(device="cuda").manual_seed(1)
+    q, k = (t.randn(1, 1, nb * b, D, generator=gen, device="cuda", dtype=t.float32).to(t.bfloat16)
+            for _ in range(2))
+    mass = t.zeros((1, 1, nb, nb), dtype=t.float32, device="cuda")
+    B.cosa_block_mass(B.Problem(1, 1, 1, nb * b, D, b, b // 8), q, k, mass)
+    assert bool(((mass.tril().sum(-1) - b).abs() < 1e-4 * b).all())
+    for i in (0, 1, 4095, nb - 1):
+        x = q[0, 0, i * b:(i + 1) * b].double() @ k[0, 0, :(i + 1) * b].double().T / D ** 0.5
+        x[:, i * b:].masked_fill_(t.ones(b, b, dtype=t.bool, device="cuda").triu(1), float("-inf"))
+        ref = t.softmax(x, 1).view(b, i + 1, b).sum((0, 2))
+        np.testing.assert_allclose(mass[0, 0, i, :i + 1].cpu().numpy(), ref.cpu().numpy(), rtol=2e-4)
+    with pytest.raises(B.CosaError) as e:
+        B.cosa_block_mass(B.Problem(1, 1, 1, (nb + 1) * b, D, b, b // 8), q, k, mass)
+    assert e.value.status == B.COSA_ERR_UNSUPPORTED
