@@ -897,11 +897,15 @@ void launch_t(const Shape& sh, AttnParams& P, const SeqPack& pack, int cus, hipS
 
 // Two heads per workgroup where the group size is even, unless there are few tiles, at most three
 // head pairs for every two CUs: single heads then spread over the CUs more evenly, and a head's walk
-// does not wait for its partner's (pairs / single heads, us: dense, 4 / 1 heads, 8K tokens (128 pairs)
-// 168 / 135; 32 / 8 heads, 17 blocks (272): dense 57.2 / 52.2, masked 40.2 / 36.9, prefill 36.1 / 33.1;
-// 24 blocks (384): 85.4 / 82.0, 53.6 / 50.7, 45.9 / 44.1; 32 blocks (512): prefill 68.0 / 69.3).
-// 64-token blocks: list walks of up to one pair per CU only (dense, 4 / 1 heads, 64 blocks 72 / 75;
-// their pages are short, and fetching them once for both heads counts more).
+// does not wait for its partner's. Pairs / single heads, us, query / KV heads, blocks of 128 (pairs):
+//                  16/2, 24 (192)  64/8, 8 (256)  4/1, 120 (240)  8/4, 92 (368)  16/2, 56 (448)  8/4, 110 (440)
+//   dense            70.1 / 59.5    32.8 / 27.1     319 / 275       291 / 276       190 / 194       363 / 363
+//   masked, 40 %     48.3 / 42.2    30.5 / 26.6     196 / 171       154 / 147       109 / 107       182 / 178
+//   prefill, 40 %    46.9 / 42.8    32.5 / 28.8     134 / 121       128 / 125       102 / 104       155 / 166
+//   pages of 16      48.5 / 44.2    34.2 / 31.0     141 / 124       131 / 129       103 / 106       159 / 167
+// 64-token blocks: list walks of up to one pair per CU only (prefill, 40 %, 32 / 8 heads, 16 blocks 23.1 /
+// 22.5, 4 / 1 heads, 120 blocks 75.8 / 73.6). Elsewhere their pages are short, and fetching them once for
+// both heads counts more (4 / 1 heads, 64 blocks: dense 72.7 / 75.3, masked 42.7 / 45.2).
 template <int WALK, int PG>
 void launch_shape(const Shape& sh, AttnParams& P, const SeqPack& pack, hipStream_t stream) {
   const int cus = cu_count();
